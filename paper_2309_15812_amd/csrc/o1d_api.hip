@@ -12,6 +12,9 @@
 //    plane, for a group of images, fits in LDS (lanes over images; any
 //    stride, both discretisations, the fused backward at stride 1 rounding
 //    down);
+//  * walk kernels (o1d_walk*.h): the strip kernels' walks for every layout,
+//    stride up to 3, either sampling and any plane (K <= 63): NHWC calls, and
+//    NCHW planes past the other two;
 //  * general kernels (o1d_gen*.h): everything else the ABI accepts;
 //  * the depthwise separable block adds the pointwise convolution's matrix
 //    products on the matrix cores (o1d_pw*.h).
@@ -30,6 +33,7 @@
 #include "o1d_plane.h"
 #include "o1d_pw.h"
 #include "o1d_strip.h"
+#include "o1d_walk.h"
 
 namespace {
 
@@ -93,19 +97,48 @@ bool vec_aligned(const void* p, o1d_dtype_t dt) { return ((uintptr_t)p % (dt == 
 enum OpKind { kOpFwd = 0, kOpDgrad = 1, kOpWgrad = 2, kOpBwd = 3 };
 
 // The kernels one op runs: the strip kernels where they apply, else the
-// plane kernels, else the general kernels.  For the fused backward (kOpBwd)
+// plane kernels, the walk kernels, the general kernels.  For the fused backward (kOpBwd)
 // the route is a one-pass kernel of the same order; where none applies (the
 // route is not ok) o1d_bwd runs the input gradient's route and then the
 // weight gradient's.
-enum class Family { None, Strip, Plane, Gen };
+enum class Family { None, Strip, Plane, Walk, Gen };
 
 struct Route {
   bool ok = false;
   Family fam = Family::None;
   o1d::strip::Plan sp;
   o1d::plane::Plan pp;
+  o1d::walk::Plan wp;
   o1d::gen::Plan gp;
 };
+
+// plan_walk through a small per-thread table of the last plans: a plan tries
+// some tens of region shapes (microseconds), and one call asks for the same
+// sizes several times (workspace, route).
+o1d::walk::Plan walk_plan(int op, int layout, int N, int C, int H, int W, int K, int str, int mode, int esize) {
+  struct Slot {
+    int key[10];
+    o1d::walk::Plan plan;
+  };
+  constexpr int kSlots = 16;
+  static thread_local Slot slots[kSlots];
+  const int key[10] = {op, layout, N, C, H, W, K, str, mode, esize};
+  unsigned h = 2166136261u;
+  for (int v : key) h = (h ^ (unsigned)v) * 16777619u;
+  Slot& s = slots[(h >> 16) % kSlots];
+  if (memcmp(s.key, key, sizeof(key)) != 0) {
+    s.plan = o1d::walk::plan_walk(op, layout, N, C, H, W, K, str, mode, esize);
+    memcpy(s.key, key, sizeof(key));
+  }
+  return s.plan;
+}
+
+o1d::gen::Plan gen_plan(int op, int N, int C, int H, int W, int K, o1d_dtype_t dt, const Opts& o) {
+  const int gop = op == kOpFwd ? o1d::gen::kFwd
+                               : (op == kOpDgrad ? o1d::gen::kDgrad : (op == kOpWgrad ? o1d::gen::kWgrad : o1d::gen::kBwd));
+  return o1d::gen::plan_gen(gop, o.layout == O1D_NHWC ? o1d::gen::kNHWC : o1d::gen::kNCHW, N, C, H, W, K, o.stride,
+                            o.sampling == O1D_BILINEAR ? 1 : 0, (int)elem_size(dt));
+}
 
 Route route(int op, int N, int C, int H, int W, int K, o1d_dtype_t dt, const Opts& o, bool aligned) {
   Route r;
@@ -129,10 +162,14 @@ Route route(int op, int N, int C, int H, int W, int K, o1d_dtype_t dt, const Opt
       return r;
     }
   }
-  const int gop = op == kOpFwd ? o1d::gen::kFwd
-                               : (op == kOpDgrad ? o1d::gen::kDgrad : (op == kOpWgrad ? o1d::gen::kWgrad : o1d::gen::kBwd));
-  r.gp = o1d::gen::plan_gen(gop, o.layout == O1D_NHWC ? o1d::gen::kNHWC : o1d::gen::kNCHW, N, C, H, W, K, o.stride,
-                            sampling, (int)elem_size(dt));
+  const int lay = o.layout == O1D_NHWC ? o1d::walk::kNHWC : o1d::walk::kNCHW;
+  r.wp = walk_plan(op, lay, N, C, H, W, K, o.stride, sampling, (int)elem_size(dt));
+  if (o1d::walk::applies(r.wp, op, lay)) {
+    r.ok = true;
+    r.fam = Family::Walk;
+    return r;
+  }
+  r.gp = gen_plan(op, N, C, H, W, K, dt, o);
   if (r.gp.ok) {
     r.ok = true;
     r.fam = Family::Gen;
@@ -145,6 +182,7 @@ size_t route_parts(const Route& r) {
   switch (r.fam) {
     case Family::Strip: return (size_t)r.sp.blocks_n;
     case Family::Plane: return r.pp.parts;
+    case Family::Walk: return r.wp.parts;
     case Family::Gen: return r.gp.parts;
     default: return 0;
   }
@@ -200,6 +238,8 @@ o1d_status_t gather_entry(const char* fn, const void* in, const void* w, const f
     return hip_status(fn, o1d::launch_gather_strip((o1d::Dtype)dt, r.sp, in, w, theta, out, s));
   if (r.fam == Family::Plane)
     return hip_status(fn, o1d::launch_plane_gather((o1d::Dtype)dt, r.pp, in, w, theta, out, s));
+  if (r.fam == Family::Walk)
+    return hip_status(fn, o1d::launch_walk_gather((o1d::Dtype)dt, r.wp, (int)o.layout, in, w, theta, out, s));
   return hip_status(fn, o1d::launch_gen_gather((o1d::Dtype)dt, r.gp, (int)o.layout, in, w, theta, out, s));
 }
 
@@ -214,6 +254,8 @@ o1d_status_t wgrad_dispatch(const char* fn, const void* x, const void* dy, const
     return hip_status(fn, o1d::launch_wgrad_strip((o1d::Dtype)dt, r.sp, x, dy, theta, dw, part, s));
   if (r.fam == Family::Plane)
     return hip_status(fn, o1d::launch_plane_wgrad((o1d::Dtype)dt, r.pp, x, dy, theta, dw, part, s));
+  if (r.fam == Family::Walk)
+    return hip_status(fn, o1d::launch_walk_wgrad((o1d::Dtype)dt, r.wp, (int)o.layout, x, dy, theta, dw, part, s));
   return hip_status(fn, o1d::launch_gen_wgrad((o1d::Dtype)dt, r.gp, (int)o.layout, x, dy, theta, dw, part, s));
 }
 
@@ -240,16 +282,20 @@ o1d_status_t bwd_weight_entry(const char* fn, const void* x, const void* dy, con
   return wgrad_dispatch(fn, x, dy, theta_deg, dw, N, C, H, W, K, dtype, o, workspace, s);
 }
 
-void name_of(char* buf, size_t n, int op, const Route& r, o1d_dtype_t dt, const Opts& o) {
+// The general family goes by the table kernels' sizes, whichever of its two
+// forms runs (table or walk: see o1d::walk::applies).
+void name_of(char* buf, size_t n, int op, Route r, o1d_dtype_t dt, const Opts& o) {
   static const char* fam[] = {"gather", "gather", "wgrad", "bwd"};
   if (r.fam == Family::Strip)
     snprintf(buf, n, "strip_%s/%s/S%d/KB%d", fam[op], dt_name(dt), r.sp.S, r.sp.KB);
   else if (r.fam == Family::Plane)
     snprintf(buf, n, "plane_%s/%s/RP%d%s", fam[op], dt_name(dt), r.pp.p.RP,
              op >= kOpWgrad ? (r.pp.p.KB == 32 ? "/KB32" : (r.pp.p.KB == 64 ? "/KB64" : "/KB128")) : "");
-  else
+  else {
+    if (r.fam == Family::Walk) r.gp = gen_plan(op, r.wp.p.N, r.wp.p.C, r.wp.p.H, r.wp.p.W, r.wp.p.K, dt, o);
     snprintf(buf, n, "gen_%s/%s/%s/RP%d%s", fam[op], dt_name(dt), o.layout == O1D_NHWC ? "nhwc" : "nchw", r.gp.p.RP,
              op >= kOpWgrad ? (r.gp.p.KB == 32 ? "/KB32" : (r.gp.p.KB == 64 ? "/KB64" : "/KB128")) : "");
+  }
 }
 
 o1d_status_t bwd_entry(const char* fn, const void* x, const void* dy, const void* w, const float* theta_deg,
@@ -286,6 +332,8 @@ o1d_status_t bwd_entry(const char* fn, const void* x, const void* dy, const void
     return hip_status(fn, o1d::launch_bwd_strip((o1d::Dtype)dtype, r.sp, x, dy, w, theta_deg, dx, dw, part, s));
   if (r.fam == Family::Plane)
     return hip_status(fn, o1d::launch_plane_bwd((o1d::Dtype)dtype, r.pp, x, dy, w, theta_deg, dx, dw, part, s));
+  if (r.fam == Family::Walk)
+    return hip_status(fn, o1d::launch_walk_bwd((o1d::Dtype)dtype, r.wp, x, dy, w, theta_deg, dx, dw, part, s));
   if (r.fam == Family::Gen)
     return hip_status(fn, o1d::launch_gen_bwd((o1d::Dtype)dtype, r.gp, x, dy, w, theta_deg, dx, dw, part, s));
   st = gather_entry(fn, dy, w, theta_deg, dx, N, C, H, W, K, dtype, o, stream, -1);

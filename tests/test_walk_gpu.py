@@ -1,0 +1,86 @@
+"""GPU parity of the general family's walk form, at sizes that take it (the planner keeps it for larger calls).
+
+Same bar as test_parity_ex_gpu.py.  The cases cover planes as one tile and planes cut into regions, channel counts
+that leave a partial block of four and channel runs without vector alignment, stacked small planes, every phase count,
+both samplings, walks of one and of several chunks, and planes whose sides leave ragged strips.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2309_15812_amd import ops, synth
+from test_parity_ex_gpu import DEV, err, run_ex, run_plain
+
+pytestmark = pytest.mark.gpu
+
+EX = [
+    # N, C, H, W, K, dtype, theta, stride, layout, sampling
+    (64, 128, 14, 14, 7, "f32", "zero", 1, "nhwc", "floor"),      # small planes, stacked
+    (40, 97, 13, 9, 31, "f32", "uniform", 1, "nhwc", "floor"),    # small, ragged, a block of one channel
+    (33, 98, 14, 14, 31, "bf16", "uniform", 1, "nhwc", "bilinear"),
+    (70, 90, 7, 3, 63, "f32", "uniform", 1, "nhwc", "floor"),     # line longer than the plane
+    (2, 58, 56, 56, 31, "f32", "discrete8", 1, "nhwc", "floor"),  # one tile per channel
+    (1, 30, 130, 130, 5, "f32", "uniform", 1, "nhwc", "floor"),   # regions
+    (3, 61, 60, 57, 63, "bf16", "uniform", 1, "nhwc", "floor"),   # odd channel count: element accesses
+    (2, 57, 50, 56, 15, "bf16", "uniform", 1, "nhwc", "bilinear"),
+    (3, 30, 40, 40, 47, "f32", "uniform", 1, "nhwc", "floor"),
+    (2, 60, 100, 60, 63, "f32", "uniform", 2, "nhwc", "floor"),   # four phases
+    (2, 50, 100, 91, 31, "f32", "uniform", 3, "nhwc", "bilinear"),  # nine phases, uneven last rows and columns
+    (4, 128, 130, 129, 31, "f32", "uniform", 2, "nchw", "floor"),
+    (2, 70, 224, 230, 15, "bf16", "uniform", 3, "nchw", "bilinear"),
+    (2, 60, 56, 56, 31, "f32", "uniform", 1, "nchw", "bilinear"),
+    (1, 64, 63, 117, 63, "bf16", "uniform", 1, "nchw", "bilinear"),
+]
+PLAIN = [
+    # N, C, H, W, K, dtype, offset
+    (5, 130, 56, 56, 63, "f32", 0),   # sums of more than 32 cells
+    (6, 200, 57, 45, 15, "bf16", 0),
+    (6, 200, 57, 45, 31, "f32", 0),
+    (2, 140, 130, 71, 31, "f32", 0),  # regions
+    (3, 20, 199, 199, 51, "f32", 0),
+    (10, 70, 56, 54, 3, "bf16", 1),   # tensors without vector alignment
+    (11, 60, 56, 56, 1, "f32", 1),
+]
+
+
+@pytest.mark.parametrize("case", EX, ids=lambda c: "-".join(map(str, c)))
+def test_walk_ex(case):
+    N, C, H, W, K, dtype, theta, s, layout, sampling = case
+    run_ex(N, C, H, W, K, dtype, theta, s, layout, sampling, label=f"walk {case}")
+
+
+@pytest.mark.parametrize("case", PLAIN, ids=lambda c: "-".join(map(str, c)))
+def test_walk_plain(case):
+    N, C, H, W, K, dtype, offset = case
+    run_plain(N, C, H, W, K, dtype, offset=offset, label=f"walk {case}")
+
+
+def test_walk_keeps_channels_apart():
+    # an infinite pixel and a non-finite angle stay in their channels (four channels share a workgroup)
+    N, C, H, W, K = 2, 40, 56, 57, 31
+    d = synth.make_inputs(synth.Workload("apart", N, C, H, W, K, "f32", "uniform", "fwd+bwd", 7))
+    d["theta"][5] = np.nan
+    x = torch.from_numpy(np.ascontiguousarray(d["x"].transpose(0, 2, 3, 1))).to(DEV)
+    dy = torch.from_numpy(np.ascontiguousarray(d["dy"].transpose(0, 2, 3, 1))).to(DEV)
+    x[0, :, :, 0] = float("inf")
+    dy[1, H - 1, :, 2] = float("-inf")
+    w, th = torch.from_numpy(d["w"]).to(DEV), torch.from_numpy(d["theta"]).to(DEV)
+    y = ops.fwd_ex(x, w, th, 1, "nhwc").cpu().numpy()
+    dx = ops.bwd_input_ex(dy, w, th, (H, W), 1, "nhwc").cpu().numpy()
+    dw = ops.bwd_weight_ex(x, dy, th, K, 1, "nhwc").cpu().numpy()
+    assert np.isnan(y[..., 5]).all() and np.isnan(dx[..., 5]).all() and np.isnan(dw[5]).all()
+    keep = [c for c in range(C) if c not in (0, 2, 5)]
+    args = d["w"][keep], d["theta"][keep]
+    assert err(y[..., keep].transpose(0, 3, 1, 2), oracle.fwd(d["x"][:, keep], *args)) <= 1e-5
+    assert err(dx[..., keep].transpose(0, 3, 1, 2), oracle.bwd_input(d["dy"][:, keep], *args)) <= 1e-5
+    assert err(dw[keep], oracle.bwd_weight(d["x"][:, keep], d["dy"][:, keep], d["theta"][keep], K)) <= 1e-5
+
+
+def test_walk_weight_gradient_is_reproducible():
+    N, C, H, W, K = 3, 96, 56, 56, 31
+    x = torch.randn(N, H, W, C, device=DEV)
+    dy = torch.randn(N, H, W, C, device=DEV)
+    th = torch.rand(C, device=DEV) * 180
+    a = ops.bwd_weight_ex(x, dy, th, K, 1, "nhwc", "bilinear")
+    assert torch.equal(a, ops.bwd_weight_ex(x, dy, th, K, 1, "nhwc", "bilinear"))
