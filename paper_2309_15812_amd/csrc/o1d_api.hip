@@ -342,44 +342,7 @@ o1d_status_t bwd_entry(const char* fn, const void* x, const void* dy, const void
 }
 
 
-// ---- depthwise separable block: the pointwise convolution's products
-
-enum PwKind { kPwFwd = 0, kPwDgrad = 1, kPwWgrad = 2 };
-
-// The strided batched product of one pointwise step (see o1d_pw.h); the
-// weight gradient sums the images in groups sized so that about 1024
-// workgroups run.
-o1d::pw::Params pw_params(int kind, int N, int C, int Cout, int H, int W) {
-  o1d::pw::Params p{};
-  const int HW = H * W;
-  p.nbatch = N;
-  if (kind == kPwFwd) {  // Y_n = Wp Z_n
-    p.M = Cout; p.N = HW; p.K = C;
-    p.sA = 0; p.am = C; p.ak = 1; p.a_kc = 1;
-    p.sB = (long long)C * HW; p.bk = HW; p.bn = 1; p.b_nc = 1;
-    p.sC = (long long)Cout * HW; p.cm = HW; p.cn = 1;
-  } else if (kind == kPwDgrad) {  // dZ_n = Wp^T dY_n
-    p.M = C; p.N = HW; p.K = Cout;
-    p.sA = 0; p.am = 1; p.ak = C; p.a_kc = 0;
-    p.sB = (long long)Cout * HW; p.bk = HW; p.bn = 1; p.b_nc = 1;
-    p.sC = (long long)C * HW; p.cm = HW; p.cn = 1;
-  } else {  // dWp = sum_n dY_n Z_n^T
-    p.M = Cout; p.N = C; p.K = HW;
-    p.sA = (long long)Cout * HW; p.am = HW; p.ak = 1; p.a_kc = 1;
-    p.sB = (long long)C * HW; p.bk = 1; p.bn = HW; p.b_nc = 0;
-    p.sC = 0; p.cm = C; p.cn = 1;
-    p.sum = 1;
-  }
-  p.tm = o1d::pw::cdiv(p.M, o1d::pw::kBM);
-  p.tn = o1d::pw::cdiv(p.N, o1d::pw::kBN);
-  if (p.sum) {
-    const int tiles = p.tm * p.tn;
-    int nsplit = std::min(N, std::max(1, o1d::pw::cdiv(1024, tiles)));
-    p.per_split = o1d::pw::cdiv(N, nsplit);
-    p.nsplit = o1d::pw::cdiv(N, p.per_split);
-  }
-  return p;
-}
+// ---- depthwise separable block
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -391,7 +354,7 @@ struct DscWorkspace {
 
 DscWorkspace dsc_workspace(int N, int C, int Cout, int H, int W, int K, o1d_dtype_t dt) {
   DscWorkspace ws;
-  const o1d::pw::Params pg = pw_params(kPwWgrad, N, C, Cout, H, W);
+  const o1d::pw::Params pg = o1d::pw::plan(o1d::pw::kWgrad, N, C, Cout, H, W, (int)elem_size(dt));
   ws.dz = align256(in_elems(N, C, H, W) * elem_size(dt));
   ws.part = align256((size_t)pg.nsplit * Cout * C * sizeof(float));
   ws.dw = wgrad_workspace(N, C, H, W, K, dt, Opts());
@@ -550,7 +513,9 @@ o1d_status_t o1d_dsc_fwd(const void* x, const void* w_dw, const float* theta_deg
     return fail(O1D_ERR_INVALID, "%s: y or z overlaps another tensor", fn);
   st = gather_entry(fn, x, w_dw, theta_deg, z, N, C, H, W, K, dtype, o, stream, +1);
   if (st != O1D_OK) return st;
-  return hip_status(fn, o1d::launch_pw_gemm((o1d::Dtype)dtype, pw_params(kPwFwd, N, C, Cout, H, W), w_pw, z, y, s));
+  return hip_status(fn, o1d::launch_pw_gemm((o1d::Dtype)dtype, o1d::pw::kFwd,
+                                           o1d::pw::plan(o1d::pw::kFwd, N, C, Cout, H, W, (int)elem_size(dtype)),
+                                           w_pw, z, y, s));
 }
 
 size_t o1d_dsc_bwd_workspace_bytes(int N, int C, int Cout, int H, int W, int K, o1d_dtype_t dtype) {
@@ -599,10 +564,11 @@ o1d_status_t o1d_dsc_bwd(const void* x, const void* z, const void* dy, const voi
   void* dz = wsb;
   float* part = reinterpret_cast<float*>(wsb + ws.dz);
   void* dws = wsb + ws.dz + ws.part;
-  st = hip_status(fn, o1d::launch_pw_gemm((o1d::Dtype)dtype, pw_params(kPwDgrad, N, C, Cout, H, W), w_pw, dy, dz, s));
+  st = hip_status(fn, o1d::launch_pw_gemm((o1d::Dtype)dtype, o1d::pw::kDgrad,
+                                         o1d::pw::plan(o1d::pw::kDgrad, N, C, Cout, H, W, (int)es), w_pw, dy, dz, s));
   if (st != O1D_OK) return st;
-  const o1d::pw::Params pg = pw_params(kPwWgrad, N, C, Cout, H, W);
-  st = hip_status(fn, o1d::launch_pw_gemm((o1d::Dtype)dtype, pg, dy, z, part, s));
+  const o1d::pw::Params pg = o1d::pw::plan(o1d::pw::kWgrad, N, C, Cout, H, W, (int)es);
+  st = hip_status(fn, o1d::launch_pw_gemm((o1d::Dtype)dtype, o1d::pw::kWgrad, pg, dy, z, part, s));
   if (st != O1D_OK) return st;
   st = hip_status(fn, o1d::launch_partial_sum((o1d::Dtype)dtype, part, dw_pw, Cout * C, pg.nsplit, s));
   if (st != O1D_OK) return st;

@@ -1,17 +1,16 @@
 // Host-side plan of the pointwise (1 x 1) convolution of the oriented 1D
 // depthwise separable block (Sec. 3.2, "Computational cost analysis", and
-// Table 1's "Oriented 1D DSC"): a dense contraction over channels, run as a
-// strided batched matrix product on the matrix cores.
+// Table 1's "Oriented 1D DSC"): dense contractions over channels or pixels,
+// run as matrix products C[m][n] = sum_k A[m][k] B[k][n] on the matrix cores.
 //
-//   C_b[m][n] = sum_k A_b[m][k] B_b[k][n]
+//   kFwd    Y  = Wp   Z    M = C',  n = (image, pixel),  K = C
+//   kDgrad  dZ = Wp^T dY   M = C,   n = (image, pixel),  K = C'
+//   kWgrad  dWp = dY Z^T   M = C',  N = C,               k = (image, pixel)
 //
-// with element (m, k) of A_b at A + b sA + m am + k ak (strides in elements,
-// likewise B and C).  The block's three products:
-//   forward         Y_n  = Wp  Z_n   (M = C', N = H W, K = C, one batch per image)
-//   input gradient  dZ_n = Wp^T dY_n (M = C,  N = H W, K = C')
-//   weight gradient dWp  = sum_n dY_n Z_n^T (M = C', N = C, K = H W; the
-//                   images are summed in nsplit groups whose float32
-//                   partials are added in a fixed order)
+// (image, pixel) is one index over all images, so that planes that are no
+// multiple of a tile leave no partly used tile per image.  The weight
+// gradient's k range is cut into nsplit pieces whose float32 partial results
+// are added in a fixed order.
 #pragma once
 
 #include <stddef.h>
@@ -22,36 +21,79 @@
 namespace o1d {
 namespace pw {
 
-constexpr int kThreads = 256;  // four waves, 2 x 2 over the output tile
-constexpr int kBM = 128, kBN = 128, kBK = 32;
+enum Kind { kFwd = 0, kDgrad = 1, kWgrad = 2 };
+
+constexpr int kThreads = 256;  // four waves, each 32 rows x all 128 columns of the tile
+constexpr int kTile = 128;     // tile rows and columns
+constexpr int kRowBytes = 128; // k per step: 32 float32 or 64 bfloat16
 
 struct Params {
-  int M, N, K;
-  int nbatch;                 // batches (images)
-  long long sA, sB, sC;       // batch strides
-  int am, ak, bk, bn, cm, cn;
-  int a_kc, b_nc;             // A contiguous along k (else m), B contiguous along n (else k)
-  int sum;                    // 1: batches are summed (nsplit groups of partials), 0: one output per batch
-  int nsplit, per_split;      // summed: groups of per_split batches
-  int tm, tn;                 // tiles along M and N
+  int M, K;          // output rows; contraction length (weight gradient: images x pixels)
+  long long N;       // output columns (forward, input gradient: images x pixels)
+  int HW;            // pixels per image
+  int rowsA, rowsB;  // weight gradient: channels of dY and Z; else rowsB: channels of B, M: channels of the output
+  int tm;            // tiles along M (the fastest index: they share B's columns)
+  int steps, per;    // k steps in all and per workgroup
+  int nsplit;        // weight gradient: pieces of k
+  int nblocks, xcd_per;
 };
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
+// The product for N images of C -> Cout channels; esize: bytes per element.
+inline Params plan(int kind, int N, int C, int Cout, int H, int W, int esize) {
+  Params p{};
+  p.HW = H * W;
+  const int bk = kRowBytes / esize;
+  const long long pix = (long long)N * p.HW;
+  if (kind == kWgrad) {
+    p.M = Cout;
+    p.N = C;
+    p.rowsA = Cout;
+    p.rowsB = C;
+    p.K = (int)pix;
+  } else {
+    p.M = kind == kFwd ? Cout : C;
+    p.K = kind == kFwd ? C : Cout;
+    p.rowsB = p.K;
+    p.N = pix;
+  }
+  p.tm = cdiv(p.M, kTile);
+  const int tn = (int)((p.N + kTile - 1) / kTile);
+  p.steps = cdiv(p.K, bk);
+  p.nsplit = 1;
+  if (kind == kWgrad) {
+    // pieces of k: about 1024 workgroups in float32 (short float32 sums: a
+    // piece per image of 64 gives 1.0e-6 against float64), 512 in bfloat16
+    // (half the partial results to write and add; their rounding is far below
+    // the bfloat16 result's); at least four steps each
+    const int want = cdiv(esize == 4 ? 1024 : 512, p.tm * tn);
+    p.nsplit = want < p.steps / 4 ? want : p.steps / 4;
+    if (p.nsplit < 1) p.nsplit = 1;
+  }
+  p.per = cdiv(p.steps, p.nsplit);
+  p.nsplit = cdiv(p.steps, p.per);
+  p.nblocks = p.tm * tn * p.nsplit;
+  p.xcd_per = p.nblocks % 8 == 0 ? p.nblocks / 8 : 0;
+  return p;
+}
+
 }  // namespace pw
 
 // One translation unit per storage type; see o1d_pw_kernels.h.  `out` is
-// the output tensor (sum == 0) or the float32 partials nsplit x M x N
-// (sum == 1), which launch_pw_reduce then adds into the output.
-#define O1D_PW_DECL(T)                                                                                          \
-  hipError_t launch_pw_gemm_##T(const pw::Params& p, const void* A, const void* B, void* out, hipStream_t stream);
+// the output tensor, or for kWgrad the float32 partials nsplit x M x N, which
+// launch_partial_sum then adds into the output.
+#define O1D_PW_DECL(T)                                                                                       \
+  hipError_t launch_pw_gemm_##T(int kind, const pw::Params& p, const void* A, const void* B, void* out,      \
+                                hipStream_t stream);
 O1D_PW_DECL(f32)
 O1D_PW_DECL(bf16)
 #undef O1D_PW_DECL
 
-inline hipError_t launch_pw_gemm(Dtype dt, const pw::Params& p, const void* A, const void* B, void* out,
+inline hipError_t launch_pw_gemm(Dtype dt, int kind, const pw::Params& p, const void* A, const void* B, void* out,
                                  hipStream_t stream) {
-  return dt == Dtype::F32 ? launch_pw_gemm_f32(p, A, B, out, stream) : launch_pw_gemm_bf16(p, A, B, out, stream);
+  return dt == Dtype::F32 ? launch_pw_gemm_f32(kind, p, A, B, out, stream)
+                          : launch_pw_gemm_bf16(kind, p, A, B, out, stream);
 }
 
 }  // namespace o1d

@@ -3,8 +3,9 @@
 
 namespace o1d {
 
-hipError_t launch_pw_gemm_bf16(const pw::Params& p, const void* A, const void* B, void* out, hipStream_t stream) {
-  return pw::gemm_t<uint16_t>(p, A, B, out, stream);
+hipError_t launch_pw_gemm_bf16(int kind, const pw::Params& p, const void* A, const void* B, void* out,
+                             hipStream_t stream) {
+  return pw::gemm_t<uint16_t>(kind, p, A, B, out, stream);
 }
 
 }  // namespace o1d

@@ -1,22 +1,42 @@
 // Device code of the pointwise convolution's matrix products (included by
 // o1d_pw_f32.hip and o1d_pw_bf16.hip); the host plan is in o1d_pw.h.
 //
-// A workgroup computes a 128 x 128 tile of C_b with four waves (2 x 2, each
-// a 64 x 64 block of four 32 x 32 matrix-core tiles).  Per step of 32 along
-// k the A and B tiles are staged in LDS with k contiguous (As[m][k],
-// Bs[n][k]); the next step's global loads are in flight while the matrix
-// cores work on the current one.  float32 storage multiplies on
-// v_mfma_f32_32x32x2_f32 (float32 products), bfloat16 storage on
-// v_mfma_f32_32x32x16_bf16; both accumulate in float32.
+// A workgroup computes a 128 x 128 tile of the output with four waves, each
+// 32 rows x 128 columns (four 32 x 32 matrix-core accumulators).  Per step
+// 128 bytes of k (32 float32, 64 bfloat16) of 128 rows of A and 128 columns
+// of B are staged in LDS as rows of k, 144 bytes apart, so that every LDS
+// access is a 16-byte one and eight lanes' accesses (36 words apart, or one
+// row) cover all 32 banks.  The next step's loads are in flight during a
+// step's products.  One buffer of 36 KB and three workgroups per CU: two
+// buffers with one barrier per step leave two per CU, which was slower (fwd
+// at the shape below 943 against 909 us).
+// float32 storage multiplies on v_mfma_f32_32x32x2_f32 (float32 products),
+// bfloat16 storage on v_mfma_f32_32x32x16_bf16; both accumulate in float32.
 //
-// Operand layout of a 32 x 32 tile (lane l of the wave): A row l % 32 and B
-// column l % 32, the k values split between the two half-waves (l / 32);
-// accumulator element e of lane l is row 8 (e / 4) + 4 (l / 32) + e % 4,
-// column l % 32.
+// Operands whose memory runs along rows instead of k (B of the forward and
+// the input gradient, Wp of the input gradient) are loaded as blocks of four
+// rows x 16 bytes of k per thread and transposed in registers; thread
+// (g, kg) holds rows 4 g .. 4 g + 3, and row 4 g + e lies at LDS row
+// g + 32 e.  A wave's four accumulators then hold four consecutive columns
+// per lane, which leave as one vector store.
+//
+// The k of one 16-byte LDS chunk need not be consecutive matrix-core steps:
+// half-wave h takes chunks 2 j + h of A and of B alike, element s of the two
+// chunks forming float32 step (j, s).
+//
+// What bounds it: the matrix cores in float32 (64 cycles per instruction).
+// 64 x 512 -> 512 x 56 x 56 (105 GFLOP per product), float32: forward 1158 ->
+// 909 us (116 TFLOP/s), the backward's two products 2280 -> 1721 us (122; the
+// library's largest float32 product reaches 153); bfloat16, 64 x 384 -> 384 x
+// 14 x 14: 42 -> 16 us per product.  Before, loads behind per-run range tests
+// were waited for one by one, LDS took 4-byte accesses, and every image ended
+// in a partly used tile.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <atomic>
 
 #include "o1d_device.h"
 #include "o1d_pw.h"
@@ -27,217 +47,378 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Per storage type: elements per vector access (16 bytes) and the LDS row
-// pitch (k contiguous): an odd number of words for float32, so that 32 lanes
-// reading one k of 32 rows hit 32 banks; 80-byte rows for bfloat16, so that
-// every lane's 8 consecutive k are one aligned 16-byte read.
-template <typename T>
-struct Fmt;
-template <>
-struct Fmt<float> {
-  static constexpr int V = 4, LP = kBK + 1;
-};
-template <>
-struct Fmt<uint16_t> {
-  static constexpr int V = 8, LP = kBK + 8;
-};
+constexpr int kPitch = 144;                   // bytes between LDS rows
+constexpr int kBuf = 2 * kTile * kPitch;      // one buffer: A rows, then B rows
 
 template <typename T>
-struct Vec {
-  T v[Fmt<T>::V];
+struct Fmt {
+  static constexpr int V = 16 / (int)sizeof(T);            // k per chunk
+  static constexpr int BK = kRowBytes / (int)sizeof(T);    // k per step
+  static constexpr int QW = (int)sizeof(T);                // 32-bit words of four elements
 };
 
-// V consecutive elements from p (`n` of them in range, the rest zero); one
-// vector access where all are in range and p is aligned.
-template <typename T>
-__device__ __forceinline__ Vec<T> load_run(const T* p, int n, bool aligned) {
-  constexpr int V = Fmt<T>::V;
-  Vec<T> r;
-  if (n >= V && aligned) {
-    __builtin_memcpy(&r, p, sizeof(r));  // one 16-byte load
+// Four consecutive elements as packed words: one vector access, or (runs that
+// are not whole or not aligned) the elements at p + off(e).  Loads are never
+// conditional: what a share has past the operand's end is loaded from a
+// clamped address, and only the k past the end are cleared (`clear`), in the
+// last step: a register that a load may or may not write would make the
+// compiler wait for every load before the next.
+template <typename T, bool VEC, class F>
+__device__ __forceinline__ void load_quad(const T* p, F&& off, uint32_t* w) {
+  if constexpr (VEC) {
+    __builtin_memcpy(w, __builtin_assume_aligned(p + off(0), 4 * sizeof(T)), 4 * sizeof(T));
   } else {
+    T t[4];
 #pragma unroll
-    for (int e = 0; e < V; ++e) r.v[e] = e < n ? p[e] : T(0);
+    for (int e = 0; e < 4; ++e) t[e] = p[off(e)];
+    __builtin_memcpy(w, t, sizeof(t));
   }
-  return r;
 }
 
-// A lane's share of one k-step's tiles: kLoads vector loads of A and of B.
-template <typename T>
-struct Stage {
-  static constexpr int V = Fmt<T>::V;
-  static constexpr int kLoads = kBM * kBK / V / kThreads;  // the same for B (kBN = kBM)
-  Vec<T> a[kLoads], b[kLoads];
+// A thread's share of one operand's tile: 16 words.
+// Rows of k (kc): chunks kq = t % 8 of rows t / 8 + 32 i.
+// Runs along rows (rc): rows 4 g .. 4 g + 3 (g = t % 32), chunk kg = t / 32.
+struct Share {
+  uint32_t v[16];
 };
 
-// Loads the A and B tiles of batch b at (m0, n0, k0).  Contiguous runs go to
-// consecutive lanes in groups that the LDS writes spread over all banks
-// (see store_stage).
+// Clears the elements whose k is past the operand's last (`left` of the
+// step's k exist): chunks of k (kc) or rows of k (rc).
+template <typename T, bool RC>
+__device__ __forceinline__ void clear_past(Share& s, int left) {
+  constexpr int V = Fmt<T>::V, QW = Fmt<T>::QW;
+  const int k = (RC ? threadIdx.x / 32 : threadIdx.x % 8) * V;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if constexpr (RC) {
+      if (k + i / QW >= left) s.v[i] = 0u;
+    } else if constexpr (sizeof(T) == 4) {
+      if (k + i % 4 >= left) s.v[i] = 0u;
+    } else {
+      const int e = k + 2 * (i % 4);
+      s.v[i] = e + 1 < left ? s.v[i] : (e < left ? s.v[i] & 0xffffu : 0u);
+    }
+  }
+}
+
+__device__ __forceinline__ void put16(char* lds, const uint32_t* w) {
+  u32x4 x;
+  x[0] = w[0]; x[1] = w[1]; x[2] = w[2]; x[3] = w[3];
+  *reinterpret_cast<u32x4*>(lds) = x;
+}
+
+__device__ __forceinline__ void store_kc(const Share& s, char* lds) {
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) put16(lds + (t / 8 + 32 * i) * kPitch + (t % 8) * 16, &s.v[4 * i]);
+}
+
+// rc shares hold V rows of k x four elements; the transpose picks element e
+// of every k.
 template <typename T>
-__device__ __forceinline__ void load_stage(const Params& P, const T* __restrict__ A, const T* __restrict__ B, int b,
-                                           int m0, int n0, int k0, Stage<T>& s) {
-  constexpr int V = Fmt<T>::V;
-  const T* Ab = A + b * P.sA;
-  const T* Bb = B + b * P.sB;
+__device__ __forceinline__ void store_rc(const Share& s, char* lds) {
+  const int g = threadIdx.x % 32, kg = threadIdx.x / 32;
 #pragma unroll
-  for (int i = 0; i < Stage<T>::kLoads; ++i) {
-    const int idx = threadIdx.x + i * kThreads;
-    if (P.a_kc) {
-      // runs along k: idx -> (m, kq), kBK / V runs per row
-      const int kq = idx % (kBK / V), m = idx / (kBK / V);
-      const int gm = m0 + m, gk = k0 + kq * V;
-      const T* p = Ab + (long long)gm * P.am + gk;
-      s.a[i] = load_run<T>(p, gm < P.M ? P.K - gk : 0, ((uintptr_t)p & 15) == 0);
-    } else {
-      // runs along m
-      const int mq = idx % 8 + 8 * (idx / (8 * kBK)), k = (idx / 8) % kBK;
-      const int gm = m0 + mq * V, gk = k0 + k;
-      const T* p = Ab + (long long)gk * P.ak + gm;
-      s.a[i] = load_run<T>(p, gk < P.K ? P.M - gm : 0, ((uintptr_t)p & 15) == 0);
+  for (int e = 0; e < 4; ++e) {
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (sizeof(T) == 4) {
+        w[i] = s.v[4 * i + e];
+      } else {
+        // k 2 i and 2 i + 1: halves e of the quads s.v[4 i ..] and s.v[4 i + 2 ..]
+        const uint32_t a = s.v[4 * i + (e >> 1)], b = s.v[4 * i + 2 + (e >> 1)];
+        w[i] = (e & 1) ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
+      }
     }
-    if (P.b_nc) {
-      // runs along n
-      const int nq = idx % 8 + 8 * (idx / (8 * kBK)), k = (idx / 8) % kBK;
-      const int gn = n0 + nq * V, gk = k0 + k;
-      const T* p = Bb + (long long)gk * P.bk + gn;
-      s.b[i] = load_run<T>(p, gk < P.K ? P.N - gn : 0, ((uintptr_t)p & 15) == 0);
-    } else {
-      // runs along k
-      const int kq = idx % (kBK / V), n = idx / (kBK / V);
-      const int gn = n0 + n, gk = k0 + kq * V;
-      const T* p = Bb + (long long)gn * P.bn + gk;
-      s.b[i] = load_run<T>(p, gn < P.N ? P.K - gk : 0, ((uintptr_t)p & 15) == 0);
-    }
+    put16(lds + (g + 32 * e) * kPitch + kg * 16, w);
   }
 }
 
+// Rows of Wp (contiguous along k): row r, k from k0 of this step.
+template <typename T, bool VEC>
+__device__ __forceinline__ void load_w_kc(const Params& P, const T* __restrict__ A, int row0, int k0, Share& s) {
+  constexpr int V = Fmt<T>::V, QW = Fmt<T>::QW;
+  const int t = threadIdx.x, k = k0 + (t % 8) * V;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const long long r = (long long)min(row0 + t / 8 + 32 * i, P.M - 1) * P.K;
+#pragma unroll
+    for (int q = 0; q < V / 4; ++q)
+      load_quad<T, VEC>(A, [&](int e) { return r + min(k + 4 * q + e, VEC ? P.K - 4 : P.K - 1); }, &s.v[4 * i + QW * q]);
+  }
+}
+
+// Columns of Wp (the input gradient's A: element (m, k) at k M + m).
+template <typename T, bool VEC>
+__device__ __forceinline__ void load_w_rc(const Params& P, const T* __restrict__ A, int row0, int k0, Share& s) {
+  constexpr int V = Fmt<T>::V, QW = Fmt<T>::QW;
+  const int r = row0 + 4 * (threadIdx.x % 32), k = k0 + (threadIdx.x / 32) * V;
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const long long row = (long long)min(k + i, P.K - 1) * P.M;
+    load_quad<T, VEC>(A, [&](int e) { return row + min(r + e, VEC ? P.M - 4 : P.M - 1); }, &s.v[QW * i]);
+  }
+}
+
+// B of the forward and the input gradient, and their outputs: column (image,
+// pixel), rows HW apart.  off[e]: element offset of column e of a lane's four
+// (the last column's where there is none; off[0] alone where VEC).
+template <bool VEC>
+struct Cols {
+  long long off[4];
+  bool in[4];
+  __device__ __forceinline__ Cols(const Params& P, long long col0, int ch) {
+#pragma unroll
+    for (int e = 0; e < (VEC ? 1 : 4); ++e) {
+      in[e] = col0 + e < P.N;
+      const long long g = in[e] ? col0 + e : P.N - (VEC ? 4 : 1);
+      const long long img = g / P.HW;
+      off[e] = img * ch * P.HW + (g - img * P.HW);
+    }
+  }
+};
+
+template <typename T, bool VEC>
+__device__ __forceinline__ void load_cols(const Params& P, const T* __restrict__ B, const Cols<VEC>& c, int k0, Share& s) {
+  constexpr int V = Fmt<T>::V, QW = Fmt<T>::QW;
+  const int k = k0 + (threadIdx.x / 32) * V;
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const long long row = (long long)min(k + i, P.K - 1) * P.HW;
+    load_quad<T, VEC>(B, [&](int e) { return row + c.off[e]; }, &s.v[QW * i]);
+  }
+}
+
+// The weight gradient's operands: rows are channels, k = (image, pixel).
+// A thread's chunk of k lies in quads at (img[q], p[q]) (the last quad's where
+// there is none).
 template <typename T>
-__device__ __forceinline__ void store_stage(const Params& P, const Stage<T>& s, T* As, T* Bs) {
-  constexpr int V = Fmt<T>::V, LP = Fmt<T>::LP;
+struct Pix {
+  static constexpr int NQ = Fmt<T>::V / 4;
+  int k;
+  int img[NQ], p[NQ];
+  __device__ __forceinline__ Pix(const Params& P, int k0) {
+    k = k0 + (threadIdx.x % 8) * Fmt<T>::V;
 #pragma unroll
-  for (int i = 0; i < Stage<T>::kLoads; ++i) {
-    const int idx = threadIdx.x + i * kThreads;
-    if (P.a_kc) {
-      const int kq = idx % (kBK / V), m = idx / (kBK / V);
-#pragma unroll
-      for (int e = 0; e < V; ++e) As[m * LP + kq * V + e] = s.a[i].v[e];
-    } else {
-      const int mq = idx % 8 + 8 * (idx / (8 * kBK)), k = (idx / 8) % kBK;
-#pragma unroll
-      for (int e = 0; e < V; ++e) As[(mq * V + e) * LP + k] = s.a[i].v[e];
-    }
-    if (P.b_nc) {
-      const int nq = idx % 8 + 8 * (idx / (8 * kBK)), k = (idx / 8) % kBK;
-#pragma unroll
-      for (int e = 0; e < V; ++e) Bs[(nq * V + e) * LP + k] = s.b[i].v[e];
-    } else {
-      const int kq = idx % (kBK / V), n = idx / (kBK / V);
-#pragma unroll
-      for (int e = 0; e < V; ++e) Bs[n * LP + kq * V + e] = s.b[i].v[e];
+    for (int q = 0; q < NQ; ++q) {
+      const int at = min(k + 4 * q, P.K - 1);
+      img[q] = at / P.HW;
+      p[q] = at - img[q] * P.HW;
     }
   }
-}
-
-// The wave's 64 x 64 block at (wm, wn) of the tile: acc[i][j] += A rows
-// wm + 32 i .. times B columns wn + 32 j .. over the k-step.
-__device__ __forceinline__ void mma_step(const float* As, const float* Bs, int wm, int wn, f32x16 (&acc)[2][2]) {
-  constexpr int LP = Fmt<float>::LP;
-  const int l = threadIdx.x & 63, r = l & 31, h = l >> 5;
+  __device__ __forceinline__ void next(const Params& P) {
+    k += Fmt<T>::BK;
 #pragma unroll
-  for (int kk = 0; kk < kBK; kk += 2) {
-    float a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a[i] = As[(wm + 32 * i + r) * LP + kk + h];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) b[j] = Bs[(wn + 32 * j + r) * LP + kk + h];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-  }
-}
-
-__device__ __forceinline__ void mma_step(const uint16_t* As, const uint16_t* Bs, int wm, int wn,
-                                         f32x16 (&acc)[2][2]) {
-  constexpr int LP = Fmt<uint16_t>::LP;
-  const int l = threadIdx.x & 63, r = l & 31, h = l >> 5;
-#pragma unroll
-  for (int kk = 0; kk < kBK; kk += 16) {
-    bf16x8 a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const bf16x8*>(As + (wm + 32 * i + r) * LP + kk + 8 * h);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const bf16x8*>(Bs + (wn + 32 * j + r) * LP + kk + 8 * h);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-  }
-}
-
-// sum == 0: C_b (the output, type T) for batch blockIdx.z; sum == 1: the
-// float32 partial tile of batch group blockIdx.z (batches summed).
-template <typename T>
-__global__ __launch_bounds__(kThreads) void pw_gemm(Params P, const T* __restrict__ A, const T* __restrict__ B,
-                                                    void* __restrict__ out) {
-  constexpr int LP = Fmt<T>::LP;
-  __shared__ __align__(16) T As[kBM * LP];
-  __shared__ __align__(16) T Bs[kBN * LP];
-  const int n0 = blockIdx.x * kBN, m0 = blockIdx.y * kBM;
-  const int w = threadIdx.x >> 6, wm = (w & 1) * 64, wn = (w >> 1) * 64;
-  const int b0 = P.sum ? blockIdx.z * P.per_split : blockIdx.z;
-  const int b1 = P.sum ? min(P.nbatch, b0 + P.per_split) : b0 + 1;
-  const int nk = (P.K + kBK - 1) / kBK;
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  Stage<T> s;
-  load_stage<T>(P, A, B, b0, m0, n0, 0, s);
-  for (int b = b0, t = 0; b < b1;) {
-    __syncthreads();  // the previous step's reads of the tiles are done
-    store_stage<T>(P, s, As, Bs);
-    __syncthreads();
-    // the next step: its loads are in flight during this step's products
-    int nb = b, nt = t + 1;
-    if (nt == nk) {
-      nt = 0;
-      ++nb;
-    }
-    if (nb < b1) load_stage<T>(P, A, B, nb, m0, n0, nt * kBK, s);
-    mma_step(As, Bs, wm, wn, acc);
-    b = nb;
-    t = nt;
-  }
-  const int l = threadIdx.x & 63;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n = n0 + wn + 32 * j + (l & 31);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = m0 + wm + 32 * i + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
-        if (m < P.M && n < P.N) {
-          if (P.sum)
-            static_cast<float*>(out)[((long long)blockIdx.z * P.M + m) * P.N + n] = acc[i][j][e];
-          else
-            static_cast<T*>(out)[b0 * P.sC + (long long)m * P.cm + (long long)n * P.cn] = from_f32<T>(acc[i][j][e]);
+    for (int q = 0; q < NQ; ++q) {
+      if (k + 4 * q < P.K) {
+        p[q] += Fmt<T>::BK;
+        while (p[q] >= P.HW) {
+          p[q] -= P.HW;
+          ++img[q];
         }
       }
     }
+  }
+};
+
+template <typename T, bool VEC>
+__device__ __forceinline__ void load_pix(const Params& P, const T* __restrict__ X, int rows, int row0, const Pix<T>& px,
+                                         Share& s) {
+  constexpr int QW = Fmt<T>::QW;
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = min(row0 + t / 8 + 32 * i, rows - 1);
+#pragma unroll
+    for (int q = 0; q < Pix<T>::NQ; ++q) {
+      load_quad<T, VEC>(X, [&](int e) {
+        int img = px.img[q], p = px.p[q];
+        if (!VEC && px.k + 4 * q + e < P.K) {  // elements of a run may lie in the next images
+          p += e;
+          while (p >= P.HW) {
+            p -= P.HW;
+            ++img;
+          }
+        }
+        return ((long long)img * rows + r) * P.HW + p;
+      }, &s.v[4 * i + QW * q]);
+    }
+  }
+}
+
+// One step's products of the wave's 32 x 128 block from a staged buffer.  A
+// chunk's reads are issued before the products of the chunk before it;
+// `between` (the next tile's writes and loads) runs after the first chunk's
+// products, so that the matrix cores start right after the barrier.
+struct Frag {
+  u32x4 a, b[4];
+  __device__ __forceinline__ void read(const char* a0, const char* b0, int j) {
+    a = *reinterpret_cast<const u32x4*>(a0 + 32 * j);
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) b[nb] = *reinterpret_cast<const u32x4*>(b0 + nb * 32 * kPitch + 32 * j);
+  }
+};
+
+template <typename T>
+__device__ __forceinline__ void products(const Frag& f, f32x16 (&acc)[4]) {
+  if constexpr (sizeof(T) == 4) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb)
+        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(f.a[s]), __uint_as_float(f.b[nb][s]), acc[nb], 0,
+                                                       0, 0);
+  } else {
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a),
+                                                        __builtin_bit_cast(bf16x8, f.b[nb]), acc[nb], 0, 0, 0);
+  }
 }
 
 template <typename T>
-hipError_t gemm_t(const Params& p, const void* A, const void* B, void* out, hipStream_t stream) {
-  const dim3 grid((unsigned)p.tn, (unsigned)p.tm, (unsigned)(p.sum ? p.nsplit : p.nbatch));
-  hipLaunchKernelGGL(pw_gemm<T>, grid, dim3(kThreads), 0, stream, p, static_cast<const T*>(A),
-                     static_cast<const T*>(B), out);
+__device__ __forceinline__ void multiply(const char* buf, f32x16 (&acc)[4]) {
+  const int l = threadIdx.x & 63, r = l & 31, h = l >> 5, w = threadIdx.x >> 6;
+  const char* a0 = buf + (32 * w + r) * kPitch + 16 * h;
+  const char* b0 = buf + (kTile + r) * kPitch + 16 * h;
+  constexpr int NJ = kRowBytes / 32;
+  Frag f[2];
+  f[0].read(a0, b0, 0);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    if (j + 1 < NJ) f[(j + 1) & 1].read(a0, b0, j + 1);
+    products<T>(f[j & 1], acc);
+  }
+}
+
+// VA, VB: A's and B's (and the output's) runs of four elements are whole and aligned.
+template <typename T, int KIND, bool VA, bool VB>
+__global__ __launch_bounds__(kThreads, VB ? 3 : 2) void pw_gemm(Params P, const T* __restrict__ A, const T* __restrict__ B,
+                                                       void* __restrict__ out) {
+  extern __shared__ __align__(16) char lds[];
+  constexpr int BK = Fmt<T>::BK;
+  // tiles along M are neighbours on one XCD: they share B's columns in its L2
+  const int id = P.xcd_per ? (blockIdx.x % 8) * P.xcd_per + blockIdx.x / 8 : blockIdx.x;
+  const int mt = id % P.tm, rest = id / P.tm;
+  const int split = rest % P.nsplit, nt = rest / P.nsplit;
+  const int m0 = mt * kTile;
+  const long long n0 = (long long)nt * kTile;
+  const int s0 = split * P.per, s1 = min(P.steps, s0 + P.per);
+  const Cols<VB> cols(P, KIND == kWgrad ? 0 : n0 + 4 * (threadIdx.x % 32), P.rowsB);
+  Pix<T> px(P, KIND == kWgrad ? s0 * BK : 0);
+  Share sa, sb;
+  auto load = [&](int s) __attribute__((always_inline)) {
+    if constexpr (KIND == kWgrad) {
+      load_pix<T, VA>(P, A, P.rowsA, m0, px, sa);
+      load_pix<T, VB>(P, B, P.rowsB, (int)n0, px, sb);
+      px.next(P);
+    } else {
+      if constexpr (KIND == kFwd)
+        load_w_kc<T, VA>(P, A, m0, s * BK, sa);
+      else
+        load_w_rc<T, VA>(P, A, m0, s * BK, sa);
+      load_cols<T, VB>(P, B, cols, s * BK, sb);
+    }
+  };
+  auto store = [&](char* buf, int s) __attribute__((always_inline)) {
+    const int left = P.K - s * BK;
+    if (left < BK) {
+      clear_past<T, KIND == kDgrad>(sa, left);
+      clear_past<T, KIND != kWgrad>(sb, left);
+    }
+    if constexpr (KIND == kDgrad)
+      store_rc<T>(sa, buf);
+    else
+      store_kc(sa, buf);
+    if constexpr (KIND == kWgrad)
+      store_kc(sb, buf + kTile * kPitch);
+    else
+      store_rc<T>(sb, buf + kTile * kPitch);
+  };
+  f32x16 acc[4];
+#pragma unroll
+  for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[nb][e] = 0.f;
+  load(s0);
+  for (int s = s0; s < s1; ++s) {
+    __syncthreads();  // the previous step's reads are done
+    store(lds, s);
+    load(min(s + 1, s1 - 1));  // in flight during the products (past the last step: the same again, never stored)
+    __syncthreads();
+    multiply<T>(lds, acc);
+  }
+  const int l = threadIdx.x & 63, r = l & 31, w = threadIdx.x >> 6;
+  if constexpr (KIND == kWgrad) {
+    float* o = static_cast<float*>(out) + (long long)split * P.M * P.N;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int m = m0 + 32 * w + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) {
+        const int n = (int)n0 + 32 * nb + r;
+        if (m < P.M && n < P.N) o[(long long)m * P.N + n] = acc[nb][e];
+      }
+    }
+  } else {
+    const Cols<VB> oc(P, n0 + 4 * r, P.M);
+    T* o = static_cast<T*>(out);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int row = 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
+      const int m = m0 + (KIND == kDgrad ? 4 * row + w : 32 * w + row);
+      if (m >= P.M) continue;
+      T t[4];
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) t[nb] = from_f32<T>(acc[nb][e]);
+      const long long ro = (long long)m * P.HW;
+      if constexpr (VB) {
+        if (oc.in[0]) __builtin_memcpy(__builtin_assume_aligned(o + oc.off[0] + ro, 4 * sizeof(T)), t, sizeof(t));
+      } else {
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+          if (oc.in[nb]) o[oc.off[nb] + ro] = t[nb];
+      }
+    }
+  }
+}
+
+template <typename T, int KIND, bool VA, bool VB>
+hipError_t launch_kind(const Params& p, const void* A, const void* B, void* out, hipStream_t stream) {
+  static std::atomic<int> allowed{0};
+  if (!allowed.load(std::memory_order_acquire)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pw_gemm<T, KIND, VA, VB>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kBuf);
+    if (e != hipSuccess) return e;
+    allowed.store(1, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((pw_gemm<T, KIND, VA, VB>), dim3((unsigned)p.nblocks), dim3(kThreads), kBuf, stream, p,
+                     static_cast<const T*>(A), static_cast<const T*>(B), out);
   return hipGetLastError();
+}
+
+// Runs of four elements: pixels come in fours and the tensors are aligned to
+// a run; Wp's rows (forward: K elements, input gradient: M) likewise.
+template <typename T>
+hipError_t gemm_t(int kind, const Params& p, const void* A, const void* B, void* out, hipStream_t stream) {
+  auto quads = [](const void* t) { return (uintptr_t)t % (4 * sizeof(T)) == 0; };
+  if (kind == kWgrad)
+    return p.HW % 4 == 0 && quads(A) && quads(B) ? launch_kind<T, kWgrad, true, true>(p, A, B, out, stream)
+                                                 : launch_kind<T, kWgrad, false, false>(p, A, B, out, stream);
+  const bool vb = p.HW % 4 == 0 && quads(B) && quads(out), va = (kind == kFwd ? p.K : p.M) % 4 == 0 && quads(A);
+  if (kind == kFwd) {
+    if (va) return vb ? launch_kind<T, kFwd, true, true>(p, A, B, out, stream)
+                      : launch_kind<T, kFwd, true, false>(p, A, B, out, stream);
+    return vb ? launch_kind<T, kFwd, false, true>(p, A, B, out, stream)
+              : launch_kind<T, kFwd, false, false>(p, A, B, out, stream);
+  }
+  if (va) return vb ? launch_kind<T, kDgrad, true, true>(p, A, B, out, stream)
+                    : launch_kind<T, kDgrad, true, false>(p, A, B, out, stream);
+  return vb ? launch_kind<T, kDgrad, false, true>(p, A, B, out, stream)
+            : launch_kind<T, kDgrad, false, false>(p, A, B, out, stream);
 }
 
 }  // namespace
