@@ -40,8 +40,11 @@ constexpr int kSmallS = 27;    // their tile's row stride (14 columns and a shar
 constexpr int kProgHead = 64;  // program words before the per-chunk and per-cell arrays
 constexpr int kRowWords = 64 + 256;  // first column and four cell slots of every row of the line
 
-#define O1D_WALK_STRIDES(X) X(51) X(63) X(77) X(87) X(103) X(119)
-constexpr int kStrides[] = {51, 63, 77, 87, 103, 119};
+// Odd tile row strides compiled into the kernels.  79 is the least that takes
+// 56-column planes at K = 31 with bilinear sampling (a wider tile leaves four
+// resident workgroups per CU instead of five).
+#define O1D_WALK_STRIDES(X) X(51) X(63) X(79) X(87) X(103) X(119)
+constexpr int kStrides[] = {51, 63, 79, 87, 103, 119};
 
 enum Op { kFwd = 0, kDgrad = 1, kWgrad = 2, kBwd = 3 };
 enum Layout { kNCHW = 0, kNHWC = 1 };
@@ -328,10 +331,10 @@ inline bool applies(const Plan& pl, int op, int layout) {
   if (layout == kNHWC) {
     // 32 x 128 x 7 x 7: K = 17 13 against 8 us, K = 47 13 against 17; 16 x 64 x
     // 30 x 30: K = 17 17 against 14, K = 47 23 against 27; 2 x 64 x 56 x 56,
-    // K = 5: 16 against 20
+    // K = 5: 16 against 20; 12 x 247 x 175 x 15, K = 21 (fill 0.18): 117 against 96
     if (p.small) return work >= (sums ? 5.0 : 8.0);
     if (fill >= 0.5) return out >= 3e5;
-    return work >= (sums ? 10.0 : 40.0);
+    return fill >= (sums ? 0.12 : 0.22) && work >= (sums ? 10.0 : 40.0);
   }
   if (p.mode) {
     // bilinear, 2 x 64 x 56 x 56: K = 17 21 against 19 us, K = 47 28 against
