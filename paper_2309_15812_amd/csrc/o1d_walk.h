@@ -164,7 +164,7 @@ inline Plan plan_walk(int op, int layout, int N, int C, int H, int W, int K, int
   q.prog_words = (q.prog_words + 3) & ~3;
   q.ncb = cdiv(C, teams);
   const int waves = teams * lanes / 64;
-  q.sum_words = op >= kWgrad ? lanes / 64 * q.maxch * kCell : 0;
+  q.sum_words = op >= kWgrad ? lanes / 64 * q.maxch * kCell * 2 : 0;  // doubles
   const int diag = q.small ? 0 : 9;  // columns a diagonal block spans beyond its first output
   double best_cost = 0.0;
   // region sides tried: the whole side, halves, thirds and quarters, and

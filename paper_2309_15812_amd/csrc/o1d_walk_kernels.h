@@ -843,8 +843,11 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
 
 // ---------------------------------------------------------------- weight gradients
 
-// Adds the wave's per-cell sums of chunk m into its own row of LDS sums.
-__device__ __forceinline__ void flush(float (&acc)[kCell], float* sums, int m) {
+// Adds the wave's per-cell sums of chunk m into its own row of LDS sums.  A
+// lane's chain stays at most 56 products long and the sums of the chains are
+// kept in doubles: one float chain over a workgroup's items had an error of
+// 2.5e-7 in 64 x 96 x 56 x 56 (NHWC, K = 31), 1.6e-7 so (times unchanged).
+__device__ __forceinline__ void flush(float (&acc)[kCell], double* sums, int m) {
   const int lane = threadIdx.x & 63;
   const float v = wave::sum32<0>(acc);
   if ((lane & 1) == 0) sums[m * kCell + ((lane >> 1) & (kCell - 1))] += v;
@@ -854,7 +857,7 @@ __device__ __forceinline__ void flush(float (&acc)[kCell], float* sums, int m) {
 // partial[(run C + c) K + k]: the team's cell sums folded into its taps
 // (coefficient times sum, corners and waves in a fixed order).
 template <class St>
-__device__ __forceinline__ void fold(const Params& P, const St& st, const float* sums, float* partial) {
+__device__ __forceinline__ void fold(const Params& P, const St& st, const double* sums, float* partial) {
   __syncthreads();
   if (!st.live || st.t >= P.K) return;
   const Line ln(st.theta);
@@ -868,15 +871,15 @@ __device__ __forceinline__ void fold(const Params& P, const St& st, const float*
       const int r = tp.r + s + pad;
       const int e = st.pg.ent[4 * r + tp.c + u - st.pg.bmin[r]];
       if (e < 0) continue;
-      float x = 0.f;
+      double x = 0.0;
       for (int w = 0; w < St::LANES / 64; ++w) x += sums[w * P.maxch * kCell + e];
-      v += cf * (double)x;
+      v += cf * x;
     }
   partial[((size_t)st.wk.run * P.C + st.c) * P.K + st.t] = ln.fin ? (float)v : __builtin_nanf("");
 }
 
 // Weight gradient: dy of the region in registers, x walked phase by phase.
-// A program of one chunk keeps its sums in registers to the end.
+// A program of one chunk keeps its sums in registers over a few items.
 template <typename T, int L, int S, bool SMALL>
 __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attribute__((
     amdgpu_waves_per_eu(L == kNHWC ? 2 : 3))) void walk_wgrad(Params P, const T* __restrict__ x,
@@ -885,7 +888,9 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
   extern __shared__ float smem[];
   using St = Setup<T, L, S, SMALL>;
   const St st(P, smem, static_cast<const T*>(nullptr), theta);
-  float* sums = smem + P.sum_off + st.team * P.sum_words + (st.t >> 6) * P.maxch * kCell;
+  double* const team_sums = reinterpret_cast<double*>(smem + P.sum_off + st.team * P.sum_words);
+  double* sums = team_sums + (st.t >> 6) * P.maxch * kCell;
+  constexpr int kHold = SMALL ? 3 : 1;  // items whose sums stay in registers, less one
   const int nch = st.first(P.nph), c0 = st.wk.c0;
   float acc[kCell];
   clear(acc);
@@ -904,14 +909,14 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
         }, i, true);
         for (int m = st.first(f); m < st.first(f + 1); ++m) {
           sp.sums(Chunk(st.pg, m), bk.lb, dv, acc);
-          if (nch > 1) flush(acc, sums, m);
+          if (nch > 1 || ((i - st.wk.item0) & kHold) == kHold) flush(acc, sums, m);
         }
         __syncthreads();
       }
     }
   });
   if (nch == 1) flush(acc, sums, 0);
-  fold(P, st, smem + P.sum_off + st.team * P.sum_words, partial);
+  fold(P, st, team_sums, partial);
 }
 
 // Both gradients (NCHW, stride 1, rounded down): x of the region in
@@ -927,7 +932,8 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3))) void w
   auto view = [&](const void* t) __attribute__((always_inline)) {
     return [=](const Params& Q) __attribute__((always_inline)) { return view_of<T, kNCHW>(Q, t, Q.H, Q.W, 1, 0, st.c); };
   };
-  float* sums = smem + P.sum_off + (st.t >> 6) * P.maxch * kCell;
+  double* const team_sums = reinterpret_cast<double*>(smem + P.sum_off);
+  double* sums = team_sums + (st.t >> 6) * P.maxch * kCell;
   const int nch = st.first(1);
   float acc[kCell];
   clear(acc);
@@ -942,7 +948,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3))) void w
       clear(out);
       for (int m = 0; m < nch; ++m) {
         sp.both(Chunk(st.pg, m), bk.lb, xv, out, acc);
-        if (nch > 1) flush(acc, sums, m);
+        if (nch > 1 || ((i - st.wk.item0) & 1)) flush(acc, sums, m);
       }
       __syncthreads();
       sp.put(bk, st.tl.trash, out);
@@ -951,7 +957,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3))) void w
     }
   });
   if (nch == 1) flush(acc, sums, 0);
-  fold(P, st, smem + P.sum_off, partial);
+  fold(P, st, team_sums, partial);
 }
 
 // ---------------------------------------------------------------- launch
