@@ -844,9 +844,10 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
 // ---------------------------------------------------------------- weight gradients
 
 // Adds the wave's per-cell sums of chunk m into its own row of LDS sums.  A
-// lane's chain stays at most 56 products long and the sums of the chains are
-// kept in doubles: one float chain over a workgroup's items had an error of
-// 2.5e-7 in 64 x 96 x 56 x 56 (NHWC, K = 31), 1.6e-7 so (times unchanged).
+// lane's chain is one item, at most 28 products long, and the sums of the
+// chains are kept in doubles: one float chain over a workgroup's items had an
+// error of 2.5e-7 in 64 x 96 x 56 x 56 (NHWC, K = 31), chains of 56 products
+// 1.6e-7 (times unchanged).
 __device__ __forceinline__ void flush(float (&acc)[kCell], double* sums, int m) {
   const int lane = threadIdx.x & 63;
   const float v = wave::sum32<0>(acc);
@@ -879,7 +880,6 @@ __device__ __forceinline__ void fold(const Params& P, const St& st, const double
 }
 
 // Weight gradient: dy of the region in registers, x walked phase by phase.
-// A program of one chunk keeps its sums in registers over a few items.
 template <typename T, int L, int S, bool SMALL>
 __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attribute__((
     amdgpu_waves_per_eu(L == kNHWC ? 2 : 3))) void walk_wgrad(Params P, const T* __restrict__ x,
@@ -890,8 +890,7 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
   const St st(P, smem, static_cast<const T*>(nullptr), theta);
   double* const team_sums = reinterpret_cast<double*>(smem + P.sum_off + st.team * P.sum_words);
   double* sums = team_sums + (st.t >> 6) * P.maxch * kCell;
-  constexpr int kHold = SMALL ? 3 : 1;  // items whose sums stay in registers, less one
-  const int nch = st.first(P.nph), c0 = st.wk.c0;
+  const int c0 = st.wk.c0;
   float acc[kCell];
   clear(acc);
   with_shape<S, SMALL>(st.s, [&](auto sp) __attribute__((always_inline)) {
@@ -909,13 +908,12 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
         }, i, true);
         for (int m = st.first(f); m < st.first(f + 1); ++m) {
           sp.sums(Chunk(st.pg, m), bk.lb, dv, acc);
-          if (nch > 1 || ((i - st.wk.item0) & kHold) == kHold) flush(acc, sums, m);
+          flush(acc, sums, m);
         }
         __syncthreads();
       }
     }
   });
-  if (nch == 1) flush(acc, sums, 0);
   fold(P, st, team_sums, partial);
 }
 
@@ -948,7 +946,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3))) void w
       clear(out);
       for (int m = 0; m < nch; ++m) {
         sp.both(Chunk(st.pg, m), bk.lb, xv, out, acc);
-        if (nch > 1 || ((i - st.wk.item0) & 1)) flush(acc, sums, m);
+        flush(acc, sums, m);
       }
       __syncthreads();
       sp.put(bk, st.tl.trash, out);
@@ -956,7 +954,6 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3))) void w
       st.drain(view(dx), i);
     }
   });
-  if (nch == 1) flush(acc, sums, 0);
   fold(P, st, team_sums, partial);
 }
 
