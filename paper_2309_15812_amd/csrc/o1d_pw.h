@@ -78,6 +78,42 @@ inline Params plan(int kind, int N, int C, int Cout, int H, int W, int esize) {
   return p;
 }
 
+// The weight gradient's k = (image, pixel): a thread's 16-byte chunk of k
+// (ES: bytes per element) as quads of four, the same chunk of every step from
+// k0 on.  Quad q is loaded from pixel p[q] of image img[q]; a quad past the
+// last k repeats the last one that is whole (VEC: a quad is one access of four
+// pixels of one image, so H W and every k0 are multiples of four) or the last
+// pixel (single elements).
+template <int ES, bool VEC>
+struct Pixels {
+  static constexpr int NQ = 4 / ES;
+  static constexpr int BK = kRowBytes / ES;
+  int k;
+  int img[NQ], p[NQ];
+  __host__ __device__ __forceinline__ Pixels(const Params& P, int k0) {
+    k = k0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int last = P.K - (VEC ? 4 : 1), at = k + 4 * q < last ? k + 4 * q : last;
+      img[q] = at / P.HW;
+      p[q] = at - img[q] * P.HW;
+    }
+  }
+  __host__ __device__ __forceinline__ void next(const Params& P) {
+    k += BK;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      if (k + 4 * q < P.K) {
+        p[q] += BK;
+        while (p[q] >= P.HW) {
+          p[q] -= P.HW;
+          ++img[q];
+        }
+      }
+    }
+  }
+};
+
 }  // namespace pw
 
 // One translation unit per storage type; see o1d_pw_kernels.h.  `out` is

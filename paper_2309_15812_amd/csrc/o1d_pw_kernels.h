@@ -49,6 +49,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+template <typename T, bool VEC>
+using Pix = Pixels<(int)sizeof(T), VEC>;
+
 constexpr int kPitch = 144;                   // bytes between LDS rows
 constexpr int kBuf = 2 * kTile * kPitch;      // one buffer: A rows, then B rows
 
@@ -193,47 +196,16 @@ __device__ __forceinline__ void load_cols(const Params& P, const T* __restrict__
 }
 
 // The weight gradient's operands: rows are channels, k = (image, pixel).
-// A thread's chunk of k lies in quads at (img[q], p[q]) (the last quad's where
-// there is none).
-template <typename T>
-struct Pix {
-  static constexpr int NQ = Fmt<T>::V / 4;
-  int k;
-  int img[NQ], p[NQ];
-  __device__ __forceinline__ Pix(const Params& P, int k0) {
-    k = k0 + (threadIdx.x % 8) * Fmt<T>::V;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int at = min(k + 4 * q, P.K - 1);
-      img[q] = at / P.HW;
-      p[q] = at - img[q] * P.HW;
-    }
-  }
-  __device__ __forceinline__ void next(const Params& P) {
-    k += Fmt<T>::BK;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      if (k + 4 * q < P.K) {
-        p[q] += Fmt<T>::BK;
-        while (p[q] >= P.HW) {
-          p[q] -= P.HW;
-          ++img[q];
-        }
-      }
-    }
-  }
-};
-
 template <typename T, bool VEC>
-__device__ __forceinline__ void load_pix(const Params& P, const T* __restrict__ X, int rows, int row0, const Pix<T>& px,
-                                         Share& s) {
+__device__ __forceinline__ void load_pix(const Params& P, const T* __restrict__ X, int rows, int row0,
+                                         const Pix<T, VEC>& px, Share& s) {
   constexpr int QW = Fmt<T>::QW;
   const int t = threadIdx.x;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = min(row0 + t / 8 + 32 * i, rows - 1);
 #pragma unroll
-    for (int q = 0; q < Pix<T>::NQ; ++q) {
+    for (int q = 0; q < Pix<T, VEC>::NQ; ++q) {
       load_quad<T, VEC>(X, [&](int e) {
         int img = px.img[q], p = px.p[q];
         if (!VEC && px.k + 4 * q + e < P.K) {  // elements of a run may lie in the next images
@@ -308,7 +280,7 @@ __global__ __launch_bounds__(kThreads, VB ? 3 : 2) void pw_gemm(Params P, const 
   const long long n0 = (long long)nt * kTile;
   const int s0 = split * P.per, s1 = min(P.steps, s0 + P.per);
   const Cols<VB> cols(P, KIND == kWgrad ? 0 : n0 + 4 * (threadIdx.x % 32), P.rowsB);
-  Pix<T> px(P, KIND == kWgrad ? s0 * BK : 0);
+  Pix<T, VA> px(P, KIND == kWgrad ? s0 * BK + (int)(threadIdx.x % 8) * Fmt<T>::V : 0);
   Share sa, sb;
   auto load = [&](int s) __attribute__((always_inline)) {
     if constexpr (KIND == kWgrad) {

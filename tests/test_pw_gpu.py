@@ -24,6 +24,9 @@ CASES = [
     (5, 67, 131, 7, 9, "bf16", 0),
     (40, 160, 132, 14, 14, "bf16", 0),
     (1, 1, 1, 1, 1, "f32", 0),
+    (1, 8, 8, 2, 2, "f32", 0),         # pieces of k whose first step is cut
+    (2, 8, 8, 18, 18, "f32", 0),
+    (4, 8, 12, 18, 18, "bf16", 0),
 ]
 
 

@@ -1,0 +1,82 @@
+"""The pointwise products' plan on the host: every pixel that the weight gradient's loads name.
+
+A small C++ program walks the plan of o1d_pw.h as the kernel's threads do (every piece of k, every 16-byte chunk, every
+step, and the load past the last step that is issued and never stored) and checks each quad: inside the tensor, whole
+quads aligned and within one image, and the pixel that the step's k asks for wherever that k exists.
+"""
+import os
+import subprocess
+
+import pytest
+
+from paper_2309_15812_amd import build
+
+SOURCE = r"""
+#include <stdio.h>
+#include "o1d_pw.h"
+using namespace o1d::pw;
+
+static long long checked = 0, partial = 0;
+
+template <int ES, bool VEC>
+static bool walk(int N, int C, int Cout, int H, int W) {
+  const Params P = plan(kWgrad, N, C, Cout, H, W, ES);
+  constexpr int BK = kRowBytes / ES, V = 16 / ES;
+  for (int split = 0; split < P.nsplit; ++split) {
+    const int s0 = split * P.per, s1 = P.steps < s0 + P.per ? P.steps : s0 + P.per;
+    if (P.K - s0 * BK < BK) ++partial;  // a piece whose first step is cut
+    for (int chunk = 0; chunk < 8; ++chunk) {
+      Pixels<ES, VEC> px(P, s0 * BK + chunk * V);
+      for (int s = s0; s <= s1; ++s, px.next(P))
+        for (int q = 0; q < Pixels<ES, VEC>::NQ; ++q) {
+          const int k = s * BK + chunk * V + 4 * q;
+          const int img = px.img[q], p = px.p[q], run = VEC ? 4 : 1;
+          ++checked;
+          bool ok = img >= 0 && img < N && p >= 0 && p + run <= P.HW && (!VEC || p % 4 == 0);
+          if (k < P.K) ok = ok && img == k / P.HW && p == k % P.HW;
+          if (!ok) {
+            printf("N=%d C=%d Cout=%d H=%d W=%d bytes=%d vec=%d: piece %d chunk %d step %d quad %d loads pixel %d of "
+                   "image %d\n", N, C, Cout, H, W, ES, VEC, split, chunk, s, q, p, img);
+            return false;
+          }
+        }
+    }
+  }
+  return true;
+}
+
+int main() {
+  const int planes[][2] = {{1, 1}, {1, 4}, {2, 2}, {3, 5}, {4, 4}, {6, 6}, {7, 7}, {7, 8}, {9, 11}, {10, 10}, {14, 14},
+                           {18, 18}, {27, 24}, {28, 28}, {45, 37}, {56, 56}};
+  const int images[] = {1, 2, 3, 4, 5, 7, 9, 14, 16, 33, 36, 40, 64};
+  const int chans[][2] = {{8, 8}, {64, 64}, {100, 36}, {384, 384}, {512, 512}};
+  bool ok = true;
+  for (auto& hw : planes)
+    for (int n : images)
+      for (auto& c : chans) {
+        const int H = hw[0], W = hw[1];
+        ok = ok && walk<4, false>(n, c[0], c[1], H, W) && walk<2, false>(n, c[0], c[1], H, W);
+        if (H * W % 4 == 0) ok = ok && walk<4, true>(n, c[0], c[1], H, W) && walk<2, true>(n, c[0], c[1], H, W);
+      }
+  printf("%s: %lld quads, %lld pieces that start on a cut step\n", ok ? "ok" : "bad", checked, partial);
+  return ok && partial > 0 ? 0 : 1;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def compile_run(tmp_path_factory):
+    def go(source):
+        d = tmp_path_factory.mktemp("pw")
+        src, exe = d / "t.cpp", d / "t"
+        src.write_text(source)
+        rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.HIPCC)))
+        subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I", build.CSRC,
+                        "-I", os.path.join(rocm, "include"), str(src), "-o", str(exe)], check=True)
+        return subprocess.run([str(exe)], capture_output=True, text=True)
+    return go
+
+
+def test_weight_gradient_loads_stay_in_the_tensor(compile_run):
+    r = compile_run(SOURCE)
+    assert r.returncode == 0, r.stdout
