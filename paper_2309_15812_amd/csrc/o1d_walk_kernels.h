@@ -772,6 +772,7 @@ struct Setup {
     tr = __builtin_amdgcn_readfirstlane(pg.head[0]) != 0;
     base = lds_addr(smem + P.tile_off + team * P.tile_words + kGuard);
   }
+  __device__ __forceinline__ bool finite() const { return __builtin_amdgcn_readfirstlane(pg.head[2]) != 0; }
   __device__ __forceinline__ int first(int f) const { return __builtin_amdgcn_readfirstlane(pg.head[4 + f]); }
   // Item i's region of the view (view(P): the tensor's lattice view) into the tiles.
   template <class V>
@@ -799,6 +800,12 @@ template <int A>
 __device__ __forceinline__ void clear(float (&a)[A]) {
 #pragma unroll
   for (int i = 0; i < A; ++i) a[i] = 0.f;
+}
+
+template <int A>
+__device__ __forceinline__ void poison(float (&a)[A]) {
+#pragma unroll
+  for (int i = 0; i < A; ++i) a[i] = __builtin_nanf("");
 }
 
 // ---------------------------------------------------------------- gather
@@ -830,6 +837,8 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
         for (int m = st.first(f); m < st.first(f + 1); ++m) sp.gather(Chunk(st.pg, m), bk.lb, acc);
         __syncthreads();  // the tiles are free
         if (!fwd || f == nph - 1) {
+          // a non-finite angle poisons every output, those of phases without cells too
+          if (!st.finite()) poison(acc);
           sp.put(bk, st.tl.trash, acc);
           __syncthreads();  // the outputs are in the tiles
           st.drain([&](const Params& Q) __attribute__((always_inline)) {

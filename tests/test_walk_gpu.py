@@ -84,3 +84,33 @@ def test_walk_weight_gradient_is_reproducible():
     th = torch.rand(C, device=DEV) * 180
     a = ops.bwd_weight_ex(x, dy, th, K, 1, "nhwc", "bilinear")
     assert torch.equal(a, ops.bwd_weight_ex(x, dy, th, K, 1, "nhwc", "bilinear"))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("layout,sampling", [("nhwc", "floor"), ("nhwc", "bilinear"), ("nchw", "floor")])
+@pytest.mark.parametrize("stride", [1, 2, 3])
+def test_non_finite_angles_poison_their_channels(stride, layout, sampling, dtype):
+    # y and dx of such a channel are NaN at every pixel, also where no tap of any finite angle would land (stride
+    # phases without cells), dw at every tap; the other channels (four share an NHWC workgroup) stay finite.
+    # 48 x 64 x 56 x 56, K = 47: enough work for the walk form in NHWC at every stride.
+    N, C, H, W, K = 48, 64, 56, 56, 47
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    P, Q = ops.out_size(H, stride), ops.out_size(W, stride)
+    rand = torch.Generator(device=DEV).manual_seed(3)
+
+    def plane(h, w):
+        return torch.randn((N, h, w, C) if layout == "nhwc" else (N, C, h, w), generator=rand, device=DEV).to(dt)
+
+    x, dy = plane(H, W), plane(P, Q)
+    w = torch.randn(C, K, generator=rand, device=DEV).to(dt)
+    th = torch.rand(C, generator=rand, device=DEV) * 180
+    bad = [1, 2, 7, C - 1]
+    th[bad] = torch.tensor([float("nan"), float("inf"), float("-inf"), float("nan")], device=DEV)
+    how = (stride, layout, sampling)
+    y, dx = ops.fwd_ex(x, w, th, *how), ops.bwd_input_ex(dy, w, th, (H, W), *how)
+    dw = ops.bwd_weight_ex(x, dy, th, K, *how)
+    good = [c for c in range(C) if c not in bad]
+    for t in (y, dx, dw):
+        t = t.movedim(-1, 1) if layout == "nhwc" and t.dim() == 4 else t
+        t = t.movedim(1, 0) if t.dim() == 4 else t
+        assert torch.isnan(t[bad]).all() and torch.isfinite(t[good]).all()
