@@ -268,6 +268,17 @@ struct Item {
   }
 };
 
+// Rows and columns (frame) of item i's region that lie in the plane.
+struct Outputs {
+  int h, w;
+  __device__ __forceinline__ Outputs(const Params& P, int i, bool tr) {
+    const Item it(P, i);
+    const int p = min(P.BH, P.P - it.p0), q = min(P.BW, P.Q - it.q0);
+    h = tr ? q : p;
+    w = tr ? p : q;
+  }
+};
+
 // A lattice view of a tensor: element (r, c) of image n at byte
 // n img + off0 + r row + c col from base; `bytes` bounds one image's (NCHW:
 // one plane's) offsets and ncol its columns.  Rows past the plane's end and
@@ -672,6 +683,22 @@ struct Steps {
                                                                    grid(out), acc);
     });
   }
+  // Cell i's sum over the block's positions that hold outputs (frame rows below
+  // hv, columns below wv) alone.
+  static __device__ __forceinline__ float sum_inside(const Chunk& ch, int i, const Block& blk, const Vals& dv, int hv,
+                                                     int wv) {
+    const Block bk = fresh(blk);
+    const uint32_t a = bk.lb + (uint32_t)__builtin_amdgcn_readlane((int)ch.vrb, i) + 4u * (uint32_t)(i * ST);
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const float x = lds_load(a + 4u * (uint32_t)(r * ST + k));
+        if (bk.b0 + r < hv && (unsigned)(bk.j0 + SD * r + k) < (unsigned)wv) s = fmaf(dv[r * NC + k], x, s);
+      }
+    return s;
+  }
   // The block's positions (opaque to the optimiser: the tests of a ragged
   // block do not change from item to item, and hoisted out of the item loop
   // they would hold a mask per position).
@@ -857,9 +884,21 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
 // chains are kept in doubles: one float chain over a workgroup's items had an
 // error of 2.5e-7 in 64 x 96 x 56 x 56 (NHWC, K = 31), chains of 56 products
 // 1.6e-7 (times unchanged).
-__device__ __forceinline__ void flush(float (&acc)[kCell], double* sums, int m) {
+//
+// Strips reach past the region and lanes without a task walk a real block, all
+// times a zero, which an infinite or NaN pixel turns into NaN.  A cell whose
+// sum is not finite is therefore summed again over the item's outputs alone
+// (`again(cell)`: this lane's share), so that it is what its pixels make it.
+template <class F>
+__device__ __forceinline__ void flush(float (&acc)[kCell], double* sums, int m, F&& again) {
   const int lane = threadIdx.x & 63;
-  const float v = wave::sum32<0>(acc);
+  float v = wave::sum32<0>(acc);
+  for (uint64_t bad = __ballot(!isfinite(v)); bad != 0;) {
+    const int i = (strip::lobit(bad) >> 1) & (kCell - 1);
+    const float t = strip::wave_sum(again(i));
+    if (((lane >> 1) & (kCell - 1)) == i) v = t;
+    bad &= ~(3ull << (2 * i));
+  }
   if ((lane & 1) == 0) sums[m * kCell + ((lane >> 1) & (kCell - 1))] += v;
   clear(acc);
 }
@@ -917,7 +956,10 @@ __global__ __launch_bounds__((L == kNHWC ? 4 : 1) * (SMALL ? 64 : 128)) __attrib
         }, i, true);
         for (int m = st.first(f); m < st.first(f + 1); ++m) {
           sp.sums(Chunk(st.pg, m), bk.lb, dv, acc);
-          flush(acc, sums, m);
+          flush(acc, sums, m, [&](int e) __attribute__((always_inline)) {
+            const Outputs o(fresh_params(), i, st.tr);
+            return sp.sum_inside(Chunk(st.pg, m), e, bk, dv, o.h, o.w);
+          });
         }
         __syncthreads();
       }
@@ -955,7 +997,10 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3))) void w
       clear(out);
       for (int m = 0; m < nch; ++m) {
         sp.both(Chunk(st.pg, m), bk.lb, xv, out, acc);
-        flush(acc, sums, m);
+        flush(acc, sums, m, [&](int e) __attribute__((always_inline)) {
+          const Outputs o(fresh_params(), i, st.tr);
+          return sp.sum_inside(Chunk(st.pg, m), e, bk, xv, o.h, o.w);
+        });
       }
       __syncthreads();
       sp.put(bk, st.tl.trash, out);

@@ -114,3 +114,59 @@ def test_non_finite_angles_poison_their_channels(stride, layout, sampling, dtype
         t = t.movedim(-1, 1) if layout == "nhwc" and t.dim() == 4 else t
         t = t.movedim(1, 0) if t.dim() == 4 else t
         assert torch.isnan(t[bad]).all() and torch.isfinite(t[good]).all()
+
+
+NONFINITE = [
+    # N, C, H, W, K, dtype, stride, layout, sampling
+    (8, 64, 57, 57, 31, "f32", 1, "nhwc", "floor"),       # 57 rows: two strips of 28 reach 27 rows past the plane
+    (8, 64, 57, 57, 31, "bf16", 1, "nhwc", "bilinear"),
+    (64, 70, 13, 14, 31, "f32", 1, "nhwc", "floor"),      # small planes, idle lanes
+    (40, 64, 57, 57, 47, "f32", 2, "nhwc", "floor"),
+    (4, 64, 57, 57, 31, "f32", 1, "nchw", "bilinear"),
+    (4, 128, 130, 129, 31, "f32", 2, "nchw", "floor"),    # regions that end past the plane
+    (12, 64, 57, 57, 31, "bf16", 1, "nchw", "floor"),     # also both gradients in one pass
+    (5, 130, 56, 56, 63, "f32", 1, "nchw", "floor"),
+]
+
+
+@pytest.mark.parametrize("case", NONFINITE, ids=lambda c: "-".join(map(str, c)))
+def test_weight_gradients_keep_non_finite_pixels_to_their_taps(case):
+    # an infinite or NaN pixel reaches the taps that read it and no other: same finite taps, infinities and NaN as the
+    # oracle, same values (float32: 1e-5 of the largest finite one, bfloat16: 2e-2)
+    N, C, H, W, K, dtype, s, layout, sampling = case
+    d = synth.make_inputs(synth.Workload("nonfinite", N, C, H, W, K, dtype, "uniform", "fwd+bwd", 11))
+    d["theta"][:4] = [0, 45, 112.5, 90]
+    P, Q = oracle.out_size(H, s), oracle.out_size(W, s)
+    x, dy = d["x"], d["dy"][:, :, :P, :Q].copy()
+    ys, xs = s * ((P - 1) // 2), s * ((Q - 1) // 2)
+    spots = [(0, 0), (0, s * (Q - 1)), (s * (P - 1), 0), (s * (P - 1), s * (Q - 1)), (ys, xs)]
+
+    def spoil(t, step):
+        for c, v in ((0, np.inf), (1, -np.inf), (2, np.nan), (3, np.inf), (C - 1, np.inf)):
+            p, q = spots[(c + (c == C - 1)) % 5]
+            t[c % N, c, p // step, q // step] = v
+
+    tdtype = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def put(t):
+        t = t.transpose(0, 2, 3, 1) if layout == "nhwc" else t
+        return torch.from_numpy(np.ascontiguousarray(t)).to(DEV).to(tdtype)
+
+    def same(g, r):
+        g = g.float().cpu().numpy()
+        assert (np.isnan(g) == np.isnan(r)).all() and (np.isposinf(g) == np.isposinf(r)).all()
+        assert (np.isneginf(g) == np.isneginf(r)).all()
+        fin = np.isfinite(r)
+        assert fin[:4].any() and not fin[:4].all() and fin[4:C - 1].all()
+        assert err(g[fin], r[fin]) <= (1e-5 if dtype == "f32" else 2e-2)
+
+    th = torch.from_numpy(d["theta"]).to(DEV)
+    clean = x.copy()
+    spoil(x, 1)
+    same(ops.bwd_weight_ex(put(x), put(dy), th, K, s, layout, sampling),
+         oracle.bwd_weight(x, dy, d["theta"], K, stride=s, mode=sampling))
+    if (s, layout, sampling) == (1, "nchw", "floor"):
+        # the one-pass backward holds x in registers and walks dy
+        spoil(dy, s)
+        _, dw = ops.bwd(put(clean), put(dy), torch.from_numpy(d["w"]).to(DEV).to(tdtype), th)
+        same(dw, oracle.bwd_weight(clean, dy, d["theta"], K))
