@@ -377,6 +377,7 @@ o1d_status_t check_cout(const char* fn, int Cout) {
 // Nothing needs clearing: every workgroup overwrites its whole partial row
 // before the reduction reads it.
 constexpr size_t kScratchBytes = (size_t)8 << 20;
+static_assert(kScratchBytes >= (size_t)o1d::walk::kMaxPartBytes, "the walk kernels' partial rows fit the scratch");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;

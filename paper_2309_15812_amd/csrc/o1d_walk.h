@@ -38,6 +38,7 @@ constexpr int kGuard = 16;
 constexpr int kSmall = 14;     // planes up to kSmall x kSmall: one strip of 14 rows per column, one-wave teams
 constexpr int kSmallS = 27;    // their tile's row stride (14 columns and a shared margin of 13)
 constexpr int kProgHead = 64;  // program words before the per-chunk and per-cell arrays
+constexpr long long kMaxPartBytes = 8 << 20;  // partial rows of a plain weight gradient: no more than o1d_bwd_noalloc holds
 constexpr int kRowWords = 64 + 256;  // first column and four cell slots of every row of the line
 
 // Odd tile row strides compiled into the kernels.  79 is the least that takes
@@ -285,7 +286,15 @@ inline Plan plan_walk(int op, int layout, int N, int C, int H, int W, int K, int
   const long long slots =
       256LL * resident(best.lds_bytes, waves, teams == 4 ? 2 : (op == kWgrad || op == kBwd ? 3 : 4));
   double span0 = -1.0;
-  const int lo = cdiv(p.nitem, 512);  // at most 512 partial rows
+  // at most 512 partial rows, and of the plain calls' at most kMaxPartBytes:
+  // a size must not be too large for the fixed scratch only because it walks
+  // (340 x 4142 x 39 x 39, K = 55: 9.1 MB, 0.9 MB with the table kernels)
+  int rows = 512;
+  if (op >= kWgrad && layout == kNCHW && str == 1 && mode == 0) {
+    const long long fit = kMaxPartBytes / ((long long)C * K * 4);
+    if (fit < rows) rows = fit < 1 ? 1 : (int)fit;
+  }
+  const int lo = cdiv(p.nitem, rows);
   for (int n = lo; n <= p.nitem; n += n < 64 ? 1 : n / 32) {
     const long long grid = (long long)p.ncb * cdiv(p.nitem, n);
     const double span = (double)((grid + slots - 1) / slots) * (n + 1.0);

@@ -77,3 +77,11 @@ def test_workspace_sizes_cover_every_route():
                 for smp in (0, 1):
                     b = lib.o1d_bwd_weight_ex_workspace_bytes(N, C, H, W, K, s, lay, smp, 0)
                     assert b > 0 and b % (C * K * 4) == 0
+
+
+@pytest.mark.parametrize("size", [(136, 9336, 41, 41, 57), (340, 4142, 39, 39, 55), (69, 18191, 61, 28, 63),
+                                  (131, 11303, 38, 38, 63)])
+@pytest.mark.parametrize("dtype", [_lib.O1D_F32, _lib.O1D_BF16])
+def test_partial_rows_fit_the_fixed_scratch(size, dtype):
+    # many channels and a long kernel: o1d_bwd_noalloc's 8 MiB hold the partial rows of whichever kernel runs
+    assert 0 < _lib.lib().o1d_bwd_weight_workspace_bytes(*size, dtype) <= 8 << 20
