@@ -38,7 +38,8 @@ struct Params {
   int nblocks, xcd_per;
 };
 
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+// (64-bit sums: images x pixels may be anything below 2^31)
+inline int cdiv(long long a, int b) { return (int)((a + b - 1) / b); }
 
 // The product for N images of C -> Cout channels; esize: bytes per element.
 inline Params plan(int kind, int N, int C, int Cout, int H, int W, int esize) {
@@ -59,7 +60,7 @@ inline Params plan(int kind, int N, int C, int Cout, int H, int W, int esize) {
     p.N = pix;
   }
   p.tm = cdiv(p.M, kTile);
-  const int tn = (int)((p.N + kTile - 1) / kTile);
+  const int tn = cdiv(p.N, kTile);
   p.steps = cdiv(p.K, bk);
   p.nsplit = 1;
   if (kind == kWgrad) {
@@ -78,32 +79,39 @@ inline Params plan(int kind, int N, int C, int Cout, int H, int W, int esize) {
   return p;
 }
 
+// Launch grid: a row of at most 2^22 workgroups, as the workitems of one
+// dimension stay below 2^32; the kernel drops the last row's excess.
+constexpr int kGridRow = 1 << 22;
+inline unsigned grid_x(const Params& p) { return (unsigned)(p.nblocks < kGridRow ? p.nblocks : kGridRow); }
+inline unsigned grid_y(const Params& p) { return (unsigned)cdiv(p.nblocks, kGridRow); }
+
 // The weight gradient's k = (image, pixel): a thread's 16-byte chunk of k
 // (ES: bytes per element) as quads of four, the same chunk of every step from
-// k0 on.  Quad q is loaded from pixel p[q] of image img[q]; a quad past the
-// last k repeats the last one that is whole (VEC: a quad is one access of four
-// pixels of one image, so H W and every k0 are multiples of four) or the last
-// pixel (single elements).
+// its first on, before whose k `left` remain.  Quad q is loaded from pixel
+// p[q] of image img[q]; a quad past the last k repeats the last one that is
+// whole (VEC: a quad is one access of four pixels of one image, so H W and
+// every chunk's first k are multiples of four) or the last pixel (single
+// elements).  (`left` counts down: k itself could pass 2^31.)
 template <int ES, bool VEC>
 struct Pixels {
   static constexpr int NQ = 4 / ES;
   static constexpr int BK = kRowBytes / ES;
-  int k;
+  int left;
   int img[NQ], p[NQ];
-  __host__ __device__ __forceinline__ Pixels(const Params& P, int k0) {
-    k = k0;
+  __host__ __device__ __forceinline__ Pixels(const Params& P, int left0) {
+    left = left0;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      const int last = P.K - (VEC ? 4 : 1), at = k + 4 * q < last ? k + 4 * q : last;
+      const int n = left - 4 * q, at = P.K - (n > (VEC ? 4 : 1) ? n : (VEC ? 4 : 1));
       img[q] = at / P.HW;
       p[q] = at - img[q] * P.HW;
     }
   }
   __host__ __device__ __forceinline__ void next(const Params& P) {
-    k += BK;
+    left -= BK;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      if (k + 4 * q < P.K) {
+      if (left > 4 * q) {
         p[q] += BK;
         while (p[q] >= P.HW) {
           p[q] -= P.HW;

@@ -208,7 +208,7 @@ __device__ __forceinline__ void load_pix(const Params& P, const T* __restrict__ 
     for (int q = 0; q < Pix<T, VEC>::NQ; ++q) {
       load_quad<T, VEC>(X, [&](int e) {
         int img = px.img[q], p = px.p[q];
-        if (!VEC && px.k + 4 * q + e < P.K) {  // elements of a run may lie in the next images
+        if (!VEC && px.left > 4 * q + e) {  // elements of a run may lie in the next images
           p += e;
           while (p >= P.HW) {
             p -= P.HW;
@@ -273,14 +273,16 @@ __global__ __launch_bounds__(kThreads, VB ? 3 : 2) void pw_gemm(Params P, const 
   extern __shared__ __align__(16) char lds[];
   constexpr int BK = Fmt<T>::BK;
   // tiles along M are neighbours on one XCD: they share B's columns in its L2
-  const int id = P.xcd_per ? (blockIdx.x % 8) * P.xcd_per + blockIdx.x / 8 : blockIdx.x;
+  const int b = blockIdx.y * kGridRow + blockIdx.x;
+  if (b >= P.nblocks) return;
+  const int id = P.xcd_per ? (b % 8) * P.xcd_per + b / 8 : b;
   const int mt = id % P.tm, rest = id / P.tm;
   const int split = rest % P.nsplit, nt = rest / P.nsplit;
   const int m0 = mt * kTile;
   const long long n0 = (long long)nt * kTile;
   const int s0 = split * P.per, s1 = min(P.steps, s0 + P.per);
   const Cols<VB> cols(P, KIND == kWgrad ? 0 : n0 + 4 * (threadIdx.x % 32), P.rowsB);
-  Pix<T, VA> px(P, KIND == kWgrad ? s0 * BK + (int)(threadIdx.x % 8) * Fmt<T>::V : 0);
+  Pix<T, VA> px(P, KIND == kWgrad ? P.K - s0 * BK - (int)(threadIdx.x % 8) * Fmt<T>::V : P.K);
   Share sa, sb;
   auto load = [&](int s) __attribute__((always_inline)) {
     if constexpr (KIND == kWgrad) {
@@ -367,7 +369,7 @@ hipError_t launch_kind(const Params& p, const void* A, const void* B, void* out,
     if (e != hipSuccess) return e;
     allowed.store(1, std::memory_order_release);
   }
-  hipLaunchKernelGGL((pw_gemm<T, KIND, VA, VB>), dim3((unsigned)p.nblocks), dim3(kThreads), kBuf, stream, p,
+  hipLaunchKernelGGL((pw_gemm<T, KIND, VA, VB>), dim3(grid_x(p), grid_y(p)), dim3(kThreads), kBuf, stream, p,
                      static_cast<const T*>(A), static_cast<const T*>(B), out);
   return hipGetLastError();
 }

@@ -19,17 +19,22 @@ using namespace o1d::pw;
 static long long checked = 0, partial = 0;
 
 template <int ES, bool VEC>
-static bool walk(int N, int C, int Cout, int H, int W) {
+static bool walk(int N, int C, int Cout, int H, int W, bool ends = false) {
   const Params P = plan(kWgrad, N, C, Cout, H, W, ES);
   constexpr int BK = kRowBytes / ES, V = 16 / ES;
-  for (int split = 0; split < P.nsplit; ++split) {
+  if (P.nsplit < 1 || P.per < 1 || (long long)P.steps * BK < P.K || (P.steps - 1ll) * BK >= P.K ||
+      (long long)P.per * P.nsplit < P.steps || (P.nsplit - 1ll) * P.per >= P.steps) {
+    printf("N=%d H=%d W=%d: %d steps in %d pieces of %d\n", N, H, W, P.steps, P.nsplit, P.per);
+    return false;
+  }
+  for (int split = ends ? P.nsplit - 1 : 0; split < P.nsplit; ++split) {
     const int s0 = split * P.per, s1 = P.steps < s0 + P.per ? P.steps : s0 + P.per;
     if (P.K - s0 * BK < BK) ++partial;  // a piece whose first step is cut
     for (int chunk = 0; chunk < 8; ++chunk) {
-      Pixels<ES, VEC> px(P, s0 * BK + chunk * V);
+      Pixels<ES, VEC> px(P, P.K - s0 * BK - chunk * V);
       for (int s = s0; s <= s1; ++s, px.next(P))
         for (int q = 0; q < Pixels<ES, VEC>::NQ; ++q) {
-          const int k = s * BK + chunk * V + 4 * q;
+          const long long k = (long long)s * BK + chunk * V + 4 * q;
           const int img = px.img[q], p = px.p[q], run = VEC ? 4 : 1;
           ++checked;
           bool ok = img >= 0 && img < N && p >= 0 && p + run <= P.HW && (!VEC || p % 4 == 0);
@@ -58,6 +63,19 @@ int main() {
         ok = ok && walk<4, false>(n, c[0], c[1], H, W) && walk<2, false>(n, c[0], c[1], H, W);
         if (H * W % 4 == 0) ok = ok && walk<4, true>(n, c[0], c[1], H, W) && walk<2, true>(n, c[0], c[1], H, W);
       }
+  // images x pixels just below 2^31: the last piece
+  ok = ok && walk<4, false>(2, 1, 1, 1, (1 << 30) - 1, true) && walk<2, false>(2, 1, 1, 1, (1 << 30) - 1, true) &&
+       walk<4, false>(1, 1, 8, 1, 2147483647, true) && walk<4, true>(1, 1, 8, 1, 2147483644, true) &&
+       walk<2, true>(1, 1, 8, 1, 2147483644, true);
+  // and the grid over their columns
+  for (int kind : {kFwd, kDgrad}) {
+    const Params P = plan(kind, 1, 1, 8, 1, 2147483647, 4);
+    const long long x = grid_x(P), y = grid_y(P);
+    if (P.nblocks != 1 << 24 || x * y < P.nblocks || x * kThreads >= 1ll << 32 || y > 65535 || x * y >= 1ll << 31) {
+      printf("grid %lld x %lld for %d workgroups\n", x, y, P.nblocks);
+      ok = false;
+    }
+  }
   printf("%s: %lld quads, %lld pieces that start on a cut step\n", ok ? "ok" : "bad", checked, partial);
   return ok && partial > 0 ? 0 : 1;
 }
