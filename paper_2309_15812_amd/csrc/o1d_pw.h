@@ -62,17 +62,24 @@ inline Params plan(int kind, int N, int C, int Cout, int H, int W, int esize) {
   p.tm = cdiv(p.M, kTile);
   const int tn = cdiv(p.N, kTile);
   p.steps = cdiv(p.K, bk);
-  p.nsplit = 1;
+  p.per = p.steps;
   if (kind == kWgrad) {
-    // pieces of k: about 1024 workgroups in float32 (short float32 sums: a
-    // piece per image of 64 gives 1.0e-6 against float64), 512 in bfloat16
-    // (half the partial results to write and add; their rounding is far below
-    // the bfloat16 result's); at least four steps each
+    // pieces of k: about 1024 workgroups in float32, 512 in bfloat16 (half
+    // the partial results to write and add; their rounding is far below the
+    // bfloat16 result's); at least four steps each
     const int want = cdiv(esize == 4 ? 1024 : 512, p.tm * tn);
-    p.nsplit = want < p.steps / 4 ? want : p.steps / 4;
-    if (p.nsplit < 1) p.nsplit = 1;
+    const int pieces = want < p.steps / 4 ? want : p.steps / 4;
+    p.per = cdiv(p.steps, pieces > 1 ? pieces : 1);
+    if (esize == 4) {
+      // The square of a float32 sum's error grows with the piece's length
+      // plus the number of pieces.  Pieces are cut until that is no more than
+      // with whole images (up to `want` of them): 16 x 512 -> 512 x 7 x 7 has
+      // 1.5e-7 against float64 with pieces of an image, 2.3e-7 with four steps.
+      const int whole = cdiv(N, N < want ? N : want);
+      const long long limit = (long long)p.HW * whole + cdiv(N, whole);
+      while (p.per > 1 && (long long)bk * p.per + cdiv(p.steps, p.per) > limit) --p.per;
+    }
   }
-  p.per = cdiv(p.steps, p.nsplit);
   p.nsplit = cdiv(p.steps, p.per);
   p.nblocks = p.tm * tn * p.nsplit;
   p.xcd_per = p.nblocks % 8 == 0 ? p.nblocks / 8 : 0;

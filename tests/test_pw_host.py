@@ -98,3 +98,33 @@ def compile_run(tmp_path_factory):
 def test_weight_gradient_loads_stay_in_the_tensor(compile_run):
     r = compile_run(SOURCE)
     assert r.returncode == 0, r.stdout
+
+
+SUMS = r"""
+#include <stdio.h>
+#include "o1d_pw.h"
+using namespace o1d::pw;
+// float32 pieces of k: length plus number (the square of a sum's error grows with them) no more than with whole images,
+// except where a piece is a single step already
+int main() {
+  const int planes[][2] = {{3, 3}, {7, 7}, {7, 9}, {8, 8}, {9, 21}, {12, 12}, {14, 14}, {28, 28}, {56, 56}};
+  const int chans[][2] = {{8, 8}, {64, 64}, {384, 384}, {512, 512}, {13, 253}};
+  for (auto& hw : planes)
+    for (int n : {1, 2, 5, 8, 16, 33, 64, 3000})
+      for (auto& c : chans) {
+        const Params P = plan(kWgrad, n, c[0], c[1], hw[0], hw[1], 4);
+        const int want = cdiv(1024, cdiv(c[0], kTile) * cdiv(c[1], kTile)), groups = n < want ? n : want;
+        const int images = cdiv(n, groups);
+        if (P.per > 1 && 32 * P.per + P.nsplit > images * hw[0] * hw[1] + cdiv(n, images)) {
+          printf("N=%d %dx%d C=%d: %d pieces of %d steps\n", n, hw[0], hw[1], c[0], P.nsplit, P.per);
+          return 1;
+        }
+      }
+  return 0;
+}
+"""
+
+
+def test_float32_pieces_are_no_longer_than_whole_images(compile_run):
+    r = compile_run(SUMS)
+    assert r.returncode == 0, r.stdout
