@@ -66,9 +66,11 @@ inline Params plan(int kind, int N, int C, int Cout, int H, int W, int esize) {
   if (kind == kWgrad) {
     // pieces of k: about 1024 workgroups in float32, 512 in bfloat16 (half
     // the partial results to write and add; their rounding is far below the
-    // bfloat16 result's); at least four steps each
+    // bfloat16 result's); at least four steps each, or in bfloat16 one where
+    // odd planes take element loads, whose steps are long (5 x 103 -> 17 x 11 x
+    // 11: block backward 55 -> 30 us)
     const int want = cdiv(esize == 4 ? 1024 : 512, p.tm * tn);
-    const int pieces = want < p.steps / 4 ? want : p.steps / 4;
+    const int most = esize == 2 && p.HW % 4 ? p.steps : p.steps / 4, pieces = want < most ? want : most;
     p.per = cdiv(p.steps, pieces > 1 ? pieces : 1);
     if (esize == 4) {
       // The square of a float32 sum's error grows with the piece's length
@@ -84,6 +86,14 @@ inline Params plan(int kind, int N, int C, int Cout, int H, int W, int esize) {
   p.nblocks = p.tm * tn * p.nsplit;
   p.xcd_per = p.nblocks % 8 == 0 ? p.nblocks / 8 : 0;
   return p;
+}
+
+// 16-byte chunks of k that one step holds at least (2, 4 or all 8): with fewer
+// the products stop there, and where B takes element loads a chunk's four
+// columns per thread are shared out over the threads of the absent chunks.
+__host__ __device__ inline int chunks_of(int K, int esize) {
+  const int v = 16 / esize;
+  return K <= 2 * v ? 2 : (K <= 4 * v ? 4 : 8);
 }
 
 // Launch grid: a row of at most 2^22 workgroups, as the workitems of one

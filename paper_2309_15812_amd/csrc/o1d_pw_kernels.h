@@ -18,7 +18,9 @@
 // rows x 16 bytes of k per thread and transposed in registers; thread
 // (g, kg) holds rows 4 g .. 4 g + 3, and row 4 g + e lies at LDS row
 // g + 32 e.  A wave's four accumulators then hold four consecutive columns
-// per lane, which leave as one vector store.
+// per lane, which leave as one vector store.  (Columns that take element
+// accesses, odd planes say, are g + 32 e instead: 10 x 16 -> 104 x 189 x 113,
+// bfloat16, block forward 88 -> 84 us.)
 //
 // The k of one 16-byte LDS chunk need not be consecutive matrix-core steps:
 // half-wave h takes chunks 2 j + h of A and of B alike, element s of the two
@@ -37,6 +39,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "o1d_device.h"
 #include "o1d_pw.h"
@@ -88,11 +91,12 @@ struct Share {
 };
 
 // Clears the elements whose k is past the operand's last (`left` of the
-// step's k exist): chunks of k (kc) or rows of k (rc).
+// step's k exist, the share holds those of chunk `chunk`): chunks of k (kc) or
+// rows of k (rc).
 template <typename T, bool RC>
-__device__ __forceinline__ void clear_past(Share& s, int left) {
+__device__ __forceinline__ void clear_past(Share& s, int left, int chunk) {
   constexpr int V = Fmt<T>::V, QW = Fmt<T>::QW;
-  const int k = (RC ? threadIdx.x / 32 : threadIdx.x % 8) * V;
+  const int k = chunk * V;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     if constexpr (RC) {
@@ -112,19 +116,25 @@ __device__ __forceinline__ void put16(char* lds, const uint32_t* w) {
   *reinterpret_cast<u32x4*>(lds) = x;
 }
 
+// SPREAD: row m lies at LDS row 32 (m % 4) + m / 4, as the transposed rows do,
+// so that each wave has a quarter of the rows of an operand of few.
+template <bool SPREAD = false>
 __device__ __forceinline__ void store_kc(const Share& s, char* lds) {
   const int t = threadIdx.x;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) put16(lds + (t / 8 + 32 * i) * kPitch + (t % 8) * 16, &s.v[4 * i]);
+  for (int i = 0; i < 4; ++i) {
+    const int row = t / 8 + 32 * i;
+    put16(lds + (SPREAD ? 32 * (row % 4) + row / 4 : row) * kPitch + (t % 8) * 16, &s.v[4 * i]);
+  }
 }
 
-// rc shares hold V rows of k x four elements; the transpose picks element e
-// of every k.
-template <typename T>
-__device__ __forceinline__ void store_rc(const Share& s, char* lds) {
-  const int g = threadIdx.x % 32, kg = threadIdx.x / 32;
+// rc shares hold V rows of k x E elements, in places of four; the transpose
+// picks element e of every k.  Element e is the operand's e0 + e.
+template <typename T, int E = 4>
+__device__ __forceinline__ void store_rc(const Share& s, char* lds, int chunk, int e0) {
+  const int g = threadIdx.x % 32;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
+  for (int e = 0; e < E; ++e) {
     uint32_t w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -136,9 +146,13 @@ __device__ __forceinline__ void store_rc(const Share& s, char* lds) {
         w[i] = (e & 1) ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
       }
     }
-    put16(lds + (g + 32 * e) * kPitch + kg * 16, w);
+    put16(lds + (g + 32 * (e0 + e)) * kPitch + chunk * 16, w);
   }
 }
+
+// Element accesses are many (32 loads per thread and operand in bfloat16), so
+// a wave whose rows or k all lie past the operand's end leaves them out.
+__device__ __forceinline__ int first_of_wave(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Rows of Wp (contiguous along k): row r, k from k0 of this step.
 template <typename T, bool VEC>
@@ -147,6 +161,7 @@ __device__ __forceinline__ void load_w_kc(const Params& P, const T* __restrict__
   const int t = threadIdx.x, k = k0 + (t % 8) * V;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    if (!VEC && first_of_wave(row0 + t / 8 + 32 * i) >= P.M) break;  // rows that are not stored
     const long long r = (long long)min(row0 + t / 8 + 32 * i, P.M - 1) * P.K;
 #pragma unroll
     for (int q = 0; q < V / 4; ++q)
@@ -159,6 +174,7 @@ template <typename T, bool VEC>
 __device__ __forceinline__ void load_w_rc(const Params& P, const T* __restrict__ A, int row0, int k0, Share& s) {
   constexpr int V = Fmt<T>::V, QW = Fmt<T>::QW;
   const int r = row0 + 4 * (threadIdx.x % 32), k = k0 + (threadIdx.x / 32) * V;
+  if (!VEC && first_of_wave(k) >= P.K) return;  // cleared before they are stored
 #pragma unroll
   for (int i = 0; i < V; ++i) {
     const long long row = (long long)min(k + i, P.K - 1) * P.M;
@@ -167,31 +183,44 @@ __device__ __forceinline__ void load_w_rc(const Params& P, const T* __restrict__
 }
 
 // B of the forward and the input gradient, and their outputs: column (image,
-// pixel), rows HW apart.  off[e]: element offset of column e of a lane's four
-// (the last column's where there is none; off[0] alone where VEC).
+// pixel), rows HW apart.  Thread g's four columns of a tile (n0 on), which lie
+// at LDS rows g + 32 e: 4 g + e where they are one access (VEC), else g + 32 e
+// from e0 on, so that an element access covers consecutive pixels over the lanes.  off[e]:
+// element offset of column e (the last column's where there is none; off[0]
+// alone where VEC).
 template <bool VEC>
 struct Cols {
   long long off[4];
   bool in[4];
-  __device__ __forceinline__ Cols(const Params& P, long long col0, int ch) {
+  __device__ __forceinline__ Cols(const Params& P, long long n0, int g0, int ch, int e0) {
 #pragma unroll
     for (int e = 0; e < (VEC ? 1 : 4); ++e) {
-      in[e] = col0 + e < P.N;
-      const long long g = in[e] ? col0 + e : P.N - (VEC ? 4 : 1);
-      const long long img = g / P.HW;
-      off[e] = img * ch * P.HW + (g - img * P.HW);
+      const long long col = n0 + (VEC ? 4 * g0 : g0 + 32 * (e0 + e));
+      in[e] = col < P.N;
+      const int g = (int)(in[e] ? col : P.N - (VEC ? 4 : 1));  // (images x pixels stay below 2^31)
+      const int img = g / P.HW;
+      off[e] = (long long)img * ch * P.HW + (g - img * P.HW);
     }
   }
 };
 
-template <typename T, bool VEC>
-__device__ __forceinline__ void load_cols(const Params& P, const T* __restrict__ B, const Cols<VEC>& c, int k0, Share& s) {
+// Rows k on of the first E columns.
+template <typename T, bool VEC, int E = 4>
+__device__ __forceinline__ void load_cols(const Params& P, const T* __restrict__ B, const Cols<VEC>& c, int k,
+                                          Share& s) {
   constexpr int V = Fmt<T>::V, QW = Fmt<T>::QW;
-  const int k = k0 + (threadIdx.x / 32) * V;
+  if (!VEC && first_of_wave(k) >= P.K) return;  // cleared before they are stored
 #pragma unroll
   for (int i = 0; i < V; ++i) {
     const long long row = (long long)min(k + i, P.K - 1) * P.HW;
-    load_quad<T, VEC>(B, [&](int e) { return row + c.off[e]; }, &s.v[QW * i]);
+    if constexpr (E == 4) {
+      load_quad<T, VEC>(B, [&](int e) { return row + c.off[e]; }, &s.v[QW * i]);
+    } else {
+      T t[4] = {};
+#pragma unroll
+      for (int e = 0; e < E; ++e) t[e] = B[row + c.off[e]];
+      __builtin_memcpy(&s.v[QW * i], t, sizeof(t));
+    }
   }
 }
 
@@ -203,6 +232,7 @@ __device__ __forceinline__ void load_pix(const Params& P, const T* __restrict__ 
   const int t = threadIdx.x;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    if (!VEC && first_of_wave(row0 + t / 8 + 32 * i) >= rows) break;  // rows that are not stored
     const int r = min(row0 + t / 8 + 32 * i, rows - 1);
 #pragma unroll
     for (int q = 0; q < Pix<T, VEC>::NQ; ++q) {
@@ -251,8 +281,9 @@ __device__ __forceinline__ void products(const Frag& f, f32x16 (&acc)[4]) {
   }
 }
 
-template <typename T>
-__device__ __forceinline__ void multiply(const char* buf, f32x16 (&acc)[4]) {
+// `chunks`: the step's chunks of k that hold any (all of them where SHORT is not set).
+template <typename T, bool SHORT>
+__device__ __forceinline__ void multiply(const char* buf, int chunks, f32x16 (&acc)[4]) {
   const int l = threadIdx.x & 63, r = l & 31, h = l >> 5, w = threadIdx.x >> 6;
   const char* a0 = buf + (32 * w + r) * kPitch + 16 * h;
   const char* b0 = buf + (kTile + r) * kPitch + 16 * h;
@@ -261,6 +292,7 @@ __device__ __forceinline__ void multiply(const char* buf, f32x16 (&acc)[4]) {
   f[0].read(a0, b0, 0);
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
+    if (SHORT && j > 0 && 2 * j >= chunks) break;
     if (j + 1 < NJ) f[(j + 1) & 1].read(a0, b0, j + 1);
     products<T>(f[j & 1], acc);
   }
@@ -268,10 +300,13 @@ __device__ __forceinline__ void multiply(const char* buf, f32x16 (&acc)[4]) {
 
 // VA, VB: A's and B's (and the output's) runs of four elements are whole and aligned.
 template <typename T, int KIND, bool VA, bool VB>
-__global__ __launch_bounds__(kThreads, VB ? 3 : 2) void pw_gemm(Params P, const T* __restrict__ A, const T* __restrict__ B,
+__global__ __launch_bounds__(kThreads, VB || sizeof(T) == 2 ? 3 : 2) void pw_gemm(Params P, const T* __restrict__ A, const T* __restrict__ B,
                                                        void* __restrict__ out) {
   extern __shared__ __align__(16) char lds[];
   constexpr int BK = Fmt<T>::BK;
+  // Rows of the output over the waves.  (The forward's vector stores keep 32
+  // rows per wave; its element stores, four times as many, are shared out.)
+  constexpr bool kSpread = KIND == kDgrad || (KIND == kFwd && !VB);
   // tiles along M are neighbours on one XCD: they share B's columns in its L2
   const int b = blockIdx.y * kGridRow + blockIdx.x;
   if (b >= P.nblocks) return;
@@ -281,8 +316,26 @@ __global__ __launch_bounds__(kThreads, VB ? 3 : 2) void pw_gemm(Params P, const 
   const int m0 = mt * kTile;
   const long long n0 = (long long)nt * kTile;
   const int s0 = split * P.per, s1 = min(P.steps, s0 + P.per);
-  const Cols<VB> cols(P, KIND == kWgrad ? 0 : n0 + 4 * (threadIdx.x % 32), P.rowsB);
   Pix<T, VA> px(P, KIND == kWgrad ? P.K - s0 * BK - (int)(threadIdx.x % 8) * Fmt<T>::V : P.K);
+  // B's element loads, 32 per thread in bfloat16, are shared out over all waves
+  // where few channels fill only the first chunks: E columns from e0 on of
+  // chunk `chunk` (58 x 10 -> 10 x 59 x 59, bfloat16: block forward 41 -> 29 us)
+  const int kg = threadIdx.x / 32;
+  const int nc = !VB && KIND != kWgrad ? chunks_of(P.K, (int)sizeof(T)) : 8;
+  const int chunk = kg & (nc - 1), e0 = first_of_wave(kg / nc) * (nc / 2);
+  const Cols<VB> cols(P, KIND == kWgrad ? 0 : n0, threadIdx.x % 32, P.rowsB, e0);
+  auto with_cols = [&](auto&& f) __attribute__((always_inline)) {
+    if constexpr (VB) {
+      f(std::integral_constant<int, 4>());
+    } else {
+      if (nc == 8)
+        f(std::integral_constant<int, 4>());
+      else if (nc == 4)
+        f(std::integral_constant<int, 2>());
+      else
+        f(std::integral_constant<int, 1>());
+    }
+  };
   Share sa, sb;
   auto load = [&](int s) __attribute__((always_inline)) {
     if constexpr (KIND == kWgrad) {
@@ -294,23 +347,27 @@ __global__ __launch_bounds__(kThreads, VB ? 3 : 2) void pw_gemm(Params P, const 
         load_w_kc<T, VA>(P, A, m0, s * BK, sa);
       else
         load_w_rc<T, VA>(P, A, m0, s * BK, sa);
-      load_cols<T, VB>(P, B, cols, s * BK, sb);
+      with_cols([&](auto e) __attribute__((always_inline)) {
+        load_cols<T, VB, decltype(e)::value>(P, B, cols, s * BK + chunk * Fmt<T>::V, sb);
+      });
     }
   };
   auto store = [&](char* buf, int s) __attribute__((always_inline)) {
     const int left = P.K - s * BK;
     if (left < BK) {
-      clear_past<T, KIND == kDgrad>(sa, left);
-      clear_past<T, KIND != kWgrad>(sb, left);
+      clear_past<T, KIND == kDgrad>(sa, left, KIND == kDgrad ? kg : threadIdx.x % 8);
+      clear_past<T, KIND != kWgrad>(sb, left, KIND != kWgrad ? chunk : threadIdx.x % 8);
     }
     if constexpr (KIND == kDgrad)
-      store_rc<T>(sa, buf);
+      store_rc<T>(sa, buf, kg, 0);
     else
-      store_kc(sa, buf);
+      store_kc<kSpread>(sa, buf);
     if constexpr (KIND == kWgrad)
       store_kc(sb, buf + kTile * kPitch);
     else
-      store_rc<T>(sb, buf + kTile * kPitch);
+      with_cols([&](auto e) __attribute__((always_inline)) {
+        store_rc<T, decltype(e)::value>(sb, buf + kTile * kPitch, chunk, e0);
+      });
   };
   f32x16 acc[4];
 #pragma unroll
@@ -321,9 +378,11 @@ __global__ __launch_bounds__(kThreads, VB ? 3 : 2) void pw_gemm(Params P, const 
   for (int s = s0; s < s1; ++s) {
     __syncthreads();  // the previous step's reads are done
     store(lds, s);
-    load(min(s + 1, s1 - 1));  // in flight during the products (past the last step: the same again, never stored)
+    // in flight during the products (vector loads past the last step load
+    // something in range that is never stored; element loads are left out)
+    if (VB || s + 1 < s1) load(min(s + 1, s1 - 1));
     __syncthreads();
-    multiply<T>(lds, acc);
+    multiply<T, !VB && KIND != kWgrad>(lds, nc, acc);
   }
   const int l = threadIdx.x & 63, r = l & 31, w = threadIdx.x >> 6;
   if constexpr (KIND == kWgrad) {
@@ -338,12 +397,12 @@ __global__ __launch_bounds__(kThreads, VB ? 3 : 2) void pw_gemm(Params P, const 
       }
     }
   } else {
-    const Cols<VB> oc(P, n0 + 4 * r, P.M);
+    const Cols<VB> oc(P, n0, r, P.M, 0);
     T* o = static_cast<T*>(out);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int row = 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
-      const int m = m0 + (KIND == kDgrad ? 4 * row + w : 32 * w + row);
+      const int m = m0 + (kSpread ? 4 * row + w : 32 * w + row);
       if (m >= P.M) continue;
       T t[4];
 #pragma unroll

@@ -27,6 +27,13 @@ CASES = [
     (1, 8, 8, 2, 2, "f32", 0),         # pieces of k whose first step is cut
     (2, 8, 8, 18, 18, "f32", 0),
     (4, 8, 12, 18, 18, "bf16", 0),
+    (3, 8, 17, 9, 11, "f32", 0),       # element loads of few channels: one, two and four columns per thread
+    (3, 9, 16, 9, 11, "f32", 0),
+    (4, 3, 140, 13, 13, "f32", 0),
+    (3, 16, 33, 9, 11, "bf16", 0),
+    (3, 17, 32, 9, 11, "bf16", 0),
+    (4, 10, 10, 13, 13, "bf16", 0),
+    (2, 32, 1, 7, 21, "bf16", 1),
 ]
 
 
