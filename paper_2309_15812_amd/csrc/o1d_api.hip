@@ -282,20 +282,19 @@ o1d_status_t bwd_weight_entry(const char* fn, const void* x, const void* dy, con
   return wgrad_dispatch(fn, x, dy, theta_deg, dw, N, C, H, W, K, dtype, o, workspace, s);
 }
 
-// The general family goes by the table kernels' sizes, whichever of its two
-// forms runs (table or walk: see o1d::walk::applies).
-void name_of(char* buf, size_t n, int op, Route r, o1d_dtype_t dt, const Opts& o) {
+void name_of(char* buf, size_t n, int op, const Route& r, o1d_dtype_t dt, const Opts& o) {
   static const char* fam[] = {"gather", "gather", "wgrad", "bwd"};
+  const char* lay = o.layout == O1D_NHWC ? "nhwc" : "nchw";
   if (r.fam == Family::Strip)
     snprintf(buf, n, "strip_%s/%s/S%d/KB%d", fam[op], dt_name(dt), r.sp.S, r.sp.KB);
   else if (r.fam == Family::Plane)
     snprintf(buf, n, "plane_%s/%s/RP%d%s", fam[op], dt_name(dt), r.pp.p.RP,
              op >= kOpWgrad ? (r.pp.p.KB == 32 ? "/KB32" : (r.pp.p.KB == 64 ? "/KB64" : "/KB128")) : "");
-  else {
-    if (r.fam == Family::Walk) r.gp = gen_plan(op, r.wp.p.N, r.wp.p.C, r.wp.p.H, r.wp.p.W, r.wp.p.K, dt, o);
-    snprintf(buf, n, "gen_%s/%s/%s/RP%d%s", fam[op], dt_name(dt), o.layout == O1D_NHWC ? "nhwc" : "nchw", r.gp.p.RP,
+  else if (r.fam == Family::Walk)
+    snprintf(buf, n, "walk_%s/%s/%s/S%d", fam[op], dt_name(dt), lay, r.wp.S);
+  else
+    snprintf(buf, n, "gen_%s/%s/%s/RP%d%s", fam[op], dt_name(dt), lay, r.gp.p.RP,
              op >= kOpWgrad ? (r.gp.p.KB == 32 ? "/KB32" : (r.gp.p.KB == 64 ? "/KB64" : "/KB128")) : "");
-  }
 }
 
 o1d_status_t bwd_entry(const char* fn, const void* x, const void* dy, const void* w, const float* theta_deg,
@@ -605,7 +604,7 @@ const char* o1d_kernel_variant(int i) {
   // every kernel instantiation compiled into the library, in the names
   // o1d_kernel_name uses
   struct Table {
-    char names[192][48];
+    char names[192][48];  // 182 in use
     int count = 0;
     Table() {
       for (const char* d : {"f32", "bf16"}) {
@@ -624,6 +623,17 @@ const char* o1d_kernel_variant(int i) {
               if (l[1] == 'c') snprintf(names[count++], 48, "gen_bwd/%s/%s/RP%d/KB%d", d, l, rp, kb);
             }
           }
+        for (const char* l : {"nchw", "nhwc"}) {
+          for (int S : o1d::walk::kStrides)
+            for (const char* op : {"gather", "wgrad"})
+              if (l[1] == 'c' || S <= o1d::walk::kMaxStrideNhwc)
+                snprintf(names[count++], 48, "walk_%s/%s/%s/S%d", op, d, l, S);
+          if (l[1] == 'h')
+            for (const char* op : {"gather", "wgrad"})
+              snprintf(names[count++], 48, "walk_%s/%s/%s/S%d", op, d, l, o1d::walk::kSmallS);
+          else
+            for (int S : o1d::walk::kStrides) snprintf(names[count++], 48, "walk_bwd/%s/%s/S%d", d, l, S);
+        }
         for (int rp : {2, 4}) {
           snprintf(names[count++], 48, "plane_gather/%s/RP%d", d, rp);
           for (int kb : {32, 64, 128}) {

@@ -44,8 +44,11 @@ constexpr int kRowWords = 64 + 256;  // first column and four cell slots of ever
 // Odd tile row strides compiled into the kernels.  79 is the least that takes
 // 56-column planes at K = 31 with bilinear sampling (a wider tile leaves four
 // resident workgroups per CU instead of five).
-#define O1D_WALK_STRIDES(X) X(51) X(63) X(79) X(87) X(103) X(119)
+// (Four NHWC tiles of stride 119 do not fit in LDS.)
+#define O1D_WALK_STRIDES(X) X(51) X(63) X(79) X(87) X(103)
+#define O1D_WALK_STRIDES_NCHW(X) X(119)
 constexpr int kStrides[] = {51, 63, 79, 87, 103, 119};
+constexpr int kMaxStrideNhwc = 103;
 
 enum Op { kFwd = 0, kDgrad = 1, kWgrad = 2, kBwd = 3 };
 enum Layout { kNCHW = 0, kNHWC = 1 };
@@ -203,7 +206,7 @@ inline Plan plan_walk(int op, int layout, int N, int C, int H, int W, int K, int
       } else {
         for (int s : kStrides)
           if (s >= need) {
-            S = s;
+            S = layout == kNCHW || s <= kMaxStrideNhwc ? s : 0;
             break;
           }
       }

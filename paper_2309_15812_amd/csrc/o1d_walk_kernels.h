@@ -1075,6 +1075,9 @@ hipError_t gather_t(const Plan& pl, const void* in, const void* w, const float* 
 #define O1D_CASE(SV) \
   if (pl.S == SV) return gather_launch<T, L, SV, false>(pl, in, w, theta, out, stream);
   O1D_WALK_STRIDES(O1D_CASE)
+  if constexpr (L == kNCHW) {
+    O1D_WALK_STRIDES_NCHW(O1D_CASE)
+  }
 #undef O1D_CASE
   return hipErrorInvalidValue;
 }
@@ -1087,6 +1090,9 @@ hipError_t wgrad_t(const Plan& pl, const void* x, const void* dy, const float* t
 #define O1D_CASE(SV) \
   if (pl.S == SV) return wgrad_launch<T, L, SV, false>(pl, x, dy, theta, partial, stream);
   O1D_WALK_STRIDES(O1D_CASE)
+  if constexpr (L == kNCHW) {
+    O1D_WALK_STRIDES_NCHW(O1D_CASE)
+  }
 #undef O1D_CASE
   return hipErrorInvalidValue;
 }
@@ -1097,6 +1103,7 @@ hipError_t bwd_t(const Plan& pl, const void* x, const void* dy, const void* w, c
 #define O1D_CASE(SV) \
   if (pl.S == SV) return bwd_launch<T, SV>(pl, x, dy, w, theta, dx, partial, stream);
   O1D_WALK_STRIDES(O1D_CASE)
+  O1D_WALK_STRIDES_NCHW(O1D_CASE)
 #undef O1D_CASE
   return hipErrorInvalidValue;
 }

@@ -20,11 +20,12 @@ def test_every_compiled_variant_has_a_parity_case():
 def test_planned_names_are_compiled_variants():
     known = set(_lib.kernel_variants())
     for case in variant_cases().values():
-        N, C, H, W, K, dt, layout, aligned = case
+        N, C, H, W, K, dt, layout, aligned, stride, sampling = case
         d = _lib.O1D_F32 if dt == "f32" else _lib.O1D_BF16
         lay = _lib.O1D_NHWC if layout == "nhwc" else _lib.O1D_NCHW
+        smp = _lib.O1D_BILINEAR if sampling == "bilinear" else _lib.O1D_FLOOR
         for op in (0, 1, 2):
-            for v in _lib.kernel_name(op, N, C, H, W, K, 1, lay, _lib.O1D_FLOOR, d, aligned).split("+"):
+            for v in _lib.kernel_name(op, N, C, H, W, K, stride, lay, smp, d, aligned).split("+"):
                 assert v in known, v
 
 
@@ -33,10 +34,10 @@ def test_planned_names_are_compiled_variants():
     ((0, 64, 96, 56, 56, 31), "strip_gather/f32/S77/KB32"),
     ((3, 64, 96, 56, 56, 31), "strip_bwd/f32/S77/KB32"),
     ((3, 64, 192, 28, 28, 31), "strip_bwd/f32/S51/KB32"),
-    # K = 63: strip gather; both gradients in the general one-pass kernel (the
+    # K = 63: strip gather; both gradients in the walk kernels' one pass (the
     # strip one stops at 31 cells)
     ((0, 32, 256, 56, 56, 63), "strip_gather/f32/S103/KB64"),
-    ((3, 32, 256, 56, 56, 63), "gen_bwd/f32/nchw/RP4/KB64"),
+    ((3, 32, 256, 56, 56, 63), "walk_bwd/f32/nchw/S103"),
     # 14 x 14 planes (W not a multiple of 4) with many images: plane kernels
     # (lanes over images), two rows per lane
     ((0, 64, 384, 14, 14, 31), "plane_gather/f32/RP2"),
