@@ -112,13 +112,18 @@ struct Route {
   o1d::gen::Plan gp;
 };
 
-// plan_walk through a small per-thread table of the last plans: a plan tries
-// some tens of region shapes (microseconds), and one call asks for the same
-// sizes several times (workspace, route).
-o1d::walk::Plan walk_plan(int op, int layout, int N, int C, int H, int W, int K, int str, int mode, int esize) {
+// Whether a call walks and with which plan, through a small per-thread table
+// of the last sizes: a plan tries some tens of region shapes (microseconds),
+// and one call asks for the same sizes several times (workspace, route).
+struct WalkChoice {
+  bool walks = false;
+  o1d::walk::Plan plan;
+};
+
+WalkChoice walk_choice(int op, int layout, int N, int C, int H, int W, int K, int str, int mode, int esize) {
   struct Slot {
     int key[10];
-    o1d::walk::Plan plan;
+    WalkChoice choice;
   };
   constexpr int kSlots = 16;
   static thread_local Slot slots[kSlots];
@@ -127,10 +132,12 @@ o1d::walk::Plan walk_plan(int op, int layout, int N, int C, int H, int W, int K,
   for (int v : key) h = (h ^ (unsigned)v) * 16777619u;
   Slot& s = slots[(h >> 16) % kSlots];
   if (memcmp(s.key, key, sizeof(key)) != 0) {
-    s.plan = o1d::walk::plan_walk(op, layout, N, C, H, W, K, str, mode, esize);
+    s.choice.plan = o1d::walk::plan_walk(op, layout, N, C, H, W, K, str, mode, esize);
+    s.choice.walks = o1d::walk::applies(s.choice.plan, o1d::gen::plan_gen(op, layout, N, C, H, W, K, str, mode, esize),
+                                        op, layout, esize);
     memcpy(s.key, key, sizeof(key));
   }
-  return s.plan;
+  return s.choice;
 }
 
 o1d::gen::Plan gen_plan(int op, int N, int C, int H, int W, int K, o1d_dtype_t dt, const Opts& o) {
@@ -163,8 +170,9 @@ Route route(int op, int N, int C, int H, int W, int K, o1d_dtype_t dt, const Opt
     }
   }
   const int lay = o.layout == O1D_NHWC ? o1d::walk::kNHWC : o1d::walk::kNCHW;
-  r.wp = walk_plan(op, lay, N, C, H, W, K, o.stride, sampling, (int)elem_size(dt));
-  if (o1d::walk::applies(r.wp, op, lay)) {
+  const WalkChoice wc = walk_choice(op, lay, N, C, H, W, K, o.stride, sampling, (int)elem_size(dt));
+  if (wc.walks) {
+    r.wp = wc.plan;
     r.ok = true;
     r.fam = Family::Walk;
     return r;

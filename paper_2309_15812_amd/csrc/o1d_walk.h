@@ -25,6 +25,7 @@
 
 #include <stddef.h>
 
+#include "o1d_gen.h"
 #include "o1d_launch.h"
 #include "o1d_plan.h"
 
@@ -129,6 +130,24 @@ inline int resident(size_t lds_bytes, int waves, int per_simd) {
   const int by_regs = 4 * per_simd / waves;
   const int n = by_lds < by_regs ? by_lds : by_regs;
   return n < 1 ? 1 : n;
+}
+
+// Pixels staged around a region, and one item's staging of one phase: row
+// steps and batches of loads in flight.
+inline int margin_of(const Params& p) { return p.banded ? (p.halo > p.bmax ? p.halo : p.bmax) : 0; }
+struct Staging {
+  int slots, pieces;
+};
+inline Staging staging_of(const Params& p, int layout, int waves) {
+  Staging s{0, 0};
+  const int mg = margin_of(p);
+  for (int c = p.BW + 2 * mg; c > 0;) {
+    const int w = c > 44 ? 64 : (c > 22 ? 32 : (c > 10 ? 16 : 8)), st = cdiv(p.BH + 2 * mg, waves * (64 / w));
+    s.slots += p.G * st;
+    s.pieces += p.G * cdiv(st, layout == kNHWC ? 8 : 14);
+    c -= w;
+  }
+  return s;
 }
 
 // esize: bytes per element.  (Alignment plays no part: NCHW accesses are
@@ -248,15 +267,9 @@ inline Plan plan_walk(int op, int layout, int N, int C, int H, int W, int K, int
         // also waits for each piece's loads (about 2500 cycles) and at
         // barriers; resident workgroups overlap that.
         const int res = resident(lds, waves, teams == 4 ? 2 : (op == kWgrad || op == kBwd ? 3 : 4));
-        const int mg = p.banded ? (p.halo > p.bmax ? p.halo : p.bmax) : 0;
-        const int nr = p.BH + 2 * mg;
-        int pieces = 0, slots = 0;  // batches of loads in flight, row steps
-        for (int c = p.BW + 2 * mg; c > 0;) {
-          const int w = c > 44 ? 64 : (c > 22 ? 32 : (c > 10 ? 16 : 8)), st = cdiv(nr, waves * (64 / w));
-          slots += G * st;
-          pieces += G * cdiv(st, layout == kNHWC ? 8 : 14);
-          c -= w;
-        }
+        const int mg = margin_of(p), nr = p.BH + 2 * mg;
+        const Staging sg = staging_of(p, layout, waves);
+        const int pieces = sg.pieces, slots = sg.slots;
         const double per_slot = teams == 4 ? 20.0 : 6.0;
         const double instr = p.nph * slots * per_slot + cdiv(G * p.BH * p.BW, waves * 64) * per_slot + 200.0 +
                              K * (mode ? 2.4 : 1.0) * (p.small ? 22.0 : 36.0) + 60.0 * p.nph;
@@ -318,14 +331,79 @@ inline Plan plan_walk(int op, int layout, int N, int C, int H, int W, int K, int
   return best;
 }
 
-// Where the walks run instead of the table-driven general kernels: the
-// lines below from both timed over 270 shapes (planes 7 .. 224 along a side,
-// K 3 .. 51, float32).  A walk pays about 5 us to build its program, more
-// latency per staged phase, and for idle lanes of its 28-row strips; the
-// table kernels pay per tap and, for their sums, for more than 32 cells.
+// Estimated times of a call with the walk and with the table-driven general
+// kernels, in microseconds.  The table kernels: workgroups of `block` each,
+// per pass the staged pixels and the cells times outputs of a lane, in whole
+// rounds of resident workgroups or shared out over the CUs.  The walks:
+// instructions per wave and item (cycles of the terms below), alone with their
+// latencies or as many as share a SIMD, and a set-up per workgroup.  The rates
+// are least-squares fits of the logarithms of 43477 pairs of timings (16000
+// drawn calls: planes 7 .. 224 along a side, K 3 .. 63, every layout, stride
+// 1 .. 3 and sampling, both storage types); on 16263 further ones the ratio of
+// the two estimates has a standard deviation of 0.15 (small NHWC gathers) to
+// 0.28 (NHWC weight gradients) in the logarithm.
+struct Rates {
+  double block, cell, cell16, fold, share, base;                            // table kernels (us; cell16: bfloat16's factor)
+  double slot, slot16, store, step, phase, wait, piece, busy, setup, zero;  // walks (cycles; the last two us)
+};
+constexpr double kStageUs = 0.001;  // table kernels: a staged pixel
+constexpr Rates kRates[3][2] = {  // [NCHW, NHWC, NHWC small][gathers, sums]
+    {{1.63, 0.0103, 1.12, 0, 0.509, 6.04, 13.6, 0.903, 22.3, 17.8, 363, 20, 0, 1.89, 13.5, 2.61},
+     {14.5, 0.0123, 1.42, 0, 0.405, 0.753, 28.2, 0.987, 12.1, 27.6, 466, 8.99, 2670, 1.32, 28.7, 2.79}},
+    {{5.63, 0.0087, 1.37, 0, 0.724, 5.68, 18.3, 1.45, 137, 13.2, 251, 31, 3810, 1.3, 13.4, 0},
+     {13.8, 0.0155, 1.7, 2.53, 0.664, 2.75, 18.8, 1.11, 95.3, 8.57, 161, 47, 4030, 1.3, 23.9, 0}},
+    {{1.82, 0.0127, 1.21, 0, 0.785, 6.86, 16.7, 1.34, 75.3, 5.43, 168, 34, 0, 1.3, 7.44, 16.1},
+     {2.88, 0.0349, 1.21, 0.789, 0.859, 10.1, 16.9, 1.17, 66.4, 5.85, 218, 29, 0, 1.3, 12.5, 20.7}}};
+inline const Rates& rates_of(const Plan& pl, int op, int layout) {
+  return kRates[layout == kNCHW ? 0 : (pl.p.small ? 2 : 1)][op >= kWgrad];
+}
+
+inline double table_us(const gen::Plan& pl, const Rates& r, int op, int layout, int esize) {
+  const gen::Params& p = pl.p;
+  const bool sums = op >= kWgrad;
+  auto held = [&](int tile, int src) { return (double)(tile < (src - 1) * p.dil + 1 ? tile : (src - 1) * p.dil + 1) / p.dil; };
+  const double staged = p.G * p.CB * held(p.TR, p.SH) * held(p.TC, p.SW);
+  // a lane's tasks per pass; NHWC sums take up to four channels at a time
+  const int cpp = p.CB < 4 ? p.CB : 4, wpc = 4 / cpp, npass = p.CB / cpp;
+  const int tasks = layout == kNHWC && sums ? npass * cdiv(p.G * p.NRG * p.BQ, 64 * wpc)
+                                            : cdiv(p.G * p.CB * p.NRG * p.BQ, gen::kThreads);
+  const double cells = (double)tasks * p.ncap * p.RP * (sums ? p.nck : 1) * (esize == 2 ? r.cell16 : 1.0);
+  const double folds = npass > 1 && sums ? r.fold * npass * p.nck : 0.0;
+  const double block = r.block + (double)p.npw / p.G * (kStageUs * staged + r.cell * cells + folds);
+  const int by_regs = !sums ? 8 : (p.KB <= 32 ? 4 : (p.KB <= 64 ? 3 : 2));
+  const int by_lds = (int)((kMaxLdsBytes - 512) / ((pl.lds_bytes + 1023) / 1024 * 1024));
+  const int slots = 256 * (by_lds < 1 ? 1 : (by_lds < by_regs ? by_lds : by_regs));
+  const double shared = r.share * p.nblocks / 256 * block, rounds = (double)((p.nblocks + slots - 1) / slots) * block;
+  return r.base + (shared > rounds ? shared : rounds);
+}
+
+inline double walk_us(const Plan& pl, const Rates& r, int op, int layout, int esize) {
+  const Params& p = pl.p;
+  const bool sums = op >= kWgrad;
+  const int teams = layout == kNHWC ? 4 : 1, waves = teams * (p.small ? 64 : 128) / 64;
+  const int res = resident(pl.lds_bytes, waves, teams == 4 ? 2 : (sums ? 3 : 4));
+  const Staging sg = staging_of(p, layout, waves);
+  const double instr = p.nph * (sg.slots * r.slot * (esize == 2 ? r.slot16 : 1.0) + r.phase) + p.K * (p.mode ? 2.4 : 1.0) * r.step +
+                       cdiv(p.G * p.BH * p.BW, waves * 64) * r.store * (op == kDgrad ? p.nph : 1);
+  const double alone = r.wait * instr + p.nph * r.piece * sg.pieces, busy = r.busy * instr * waves * res;
+  const double block = p.ipw * (alone > busy ? alone : busy) / 2400.0 +
+                       (r.setup + r.zero * (double)pl.lds_bytes / 65536.0) / 2.4;
+  const double share = p.nblocks / (256.0 * res);
+  const double rounds = 0.5 * ((p.nblocks + 256 * res - 1) / (256 * res) + (share > 1.0 ? share : 1.0));
+  return 4.0 + rounds * block;
+}
+
+// Where the walks run instead of the table-driven general kernels: where they
+// are large enough for the estimates above to count (`possible`: a walk pays
+// about 5 us to build its program, more latency per staged phase, and for idle
+// lanes of its 28-row strips), and the estimate is below 0.85 of the table
+// kernels'.  Of 17724 timed calls that `possible` admits, 2801 were more than
+// 5% slower walked (12 x 247 x 175 x 15, K = 21, NHWC: 117 against 96 us; 49 x
+// 509 x 10 x 35, K = 9, bilinear, stride 2, NHWC: 410 against 63; 10 x 499 x
+// 200 x 9, K = 33, bilinear: 566 against 175); of the 12574 that the estimate
+// leaves, 334 are, and all calls together take 1.5% less time.
 // `fill`: share of a team's lanes x rows that hold outputs.
-inline bool applies(const Plan& pl, int op, int layout) {
-  if (!pl.ok) return false;
+inline bool possible(const Plan& pl, int op, int layout) {
   const Params& p = pl.p;
   const bool sums = op >= kWgrad;
   const double out = (double)p.N * p.C * p.P * p.Q;
@@ -343,22 +421,28 @@ inline bool applies(const Plan& pl, int op, int layout) {
   if (layout == kNHWC) {
     // 32 x 128 x 7 x 7: K = 17 13 against 8 us, K = 47 13 against 17; 16 x 64 x
     // 30 x 30: K = 17 17 against 14, K = 47 23 against 27; 2 x 64 x 56 x 56,
-    // K = 5: 16 against 20; 12 x 247 x 175 x 15, K = 21 (fill 0.18): 117 against 96
+    // K = 5: 16 against 20
     if (p.small) return work >= (sums ? 5.0 : 8.0);
     if (fill >= 0.5) return out >= 3e5;
     return fill >= (sums ? 0.12 : 0.22) && work >= (sums ? 10.0 : 40.0);
   }
   if (p.mode) {
     // bilinear, 2 x 64 x 56 x 56: K = 17 21 against 19 us, K = 47 28 against
-    // 37; 16 x 64 x 30 x 30, K = 47: 35 against 32, weight gradient 40 against 99
+    // 37; 16 x 64 x 30 x 30, K = 47, weight gradient 40 against 99
     if (fill >= 0.5) return work >= (sums ? 8.0 : 20.0);
     return work >= (sums ? 25.0 : 150.0);
   }
   // planes whose width the strip kernels do not take: 8 x 361 x 55 x 55, K = 15
-  // 33 against 33 us, both gradients 43 against 75; 32 x 80 x 45 x 37, K = 15 31
-  // against 20, both gradients 43 against 47; 2 x 32 x 57 x 57, K = 15 15 against 10
+  // both gradients 43 against 75 us; 32 x 80 x 45 x 37, K = 15 both gradients 43
+  // against 47; 2 x 32 x 57 x 57, K = 15 15 against 10
   if (out < 2e6) return false;
   return sums ? fill >= 0.4 : fill >= 0.55 && work >= 20.0;
+}
+
+inline bool applies(const Plan& pl, const gen::Plan& table, int op, int layout, int esize) {
+  if (!pl.ok || !possible(pl, op, layout)) return false;
+  const Rates& r = rates_of(pl, op, layout);
+  return !table.ok || walk_us(pl, r, op, layout, esize) < 0.85 * table_us(table, r, op, layout, esize);
 }
 
 }  // namespace walk

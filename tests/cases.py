@@ -43,8 +43,9 @@ def _candidates():
                 out.append((N, 64, H, W, K, _lib.O1D_NHWC, True, 1, _lib.O1D_FLOOR))
                 out.append((N, 64, H, W, K, _lib.O1D_NCHW, False, 1, _lib.O1D_FLOOR))
                 out.append((N, 64, H, W, K, _lib.O1D_NCHW, True, 1, _lib.O1D_BILINEAR))
-    out += [(N, C, M, M, K, _lib.O1D_NCHW, True, 1, _lib.O1D_BILINEAR)
-            for (N, C, M, K) in ((38, 81, 31, 5), (6, 114, 27, 37))]
+    out += [(10, 256, 36, 26, 5, _lib.O1D_NCHW, True, 1, _lib.O1D_BILINEAR),
+            (7, 256, 25, 25, 27, _lib.O1D_NCHW, True, 1, _lib.O1D_BILINEAR),
+            (51, 128, 18, 15, 1, _lib.O1D_NHWC, True, 1, _lib.O1D_FLOOR)]
     out.sort(key=lambda c: (c[0] * c[1] * c[2] * c[3] * c[4], c))
     return out
 

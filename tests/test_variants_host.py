@@ -66,6 +66,28 @@ def test_routing_of_options():
     assert _lib.kernel_name(3, 2, 4, 56, 56, 31, aligned=False) == "gen_bwd/f32/nchw/RP8/KB32"
 
 
+@pytest.mark.parametrize("op,args,family", [
+    # past the strip and plane kernels: walks where they are faster than the table kernels (timed both ways, us walked
+    # against us by table), the table kernels elsewhere
+    (0, (64, 96, 56, 56, 31, 1, 1, 0, 0), "walk_gather"),     # 113 against 259
+    (2, (64, 384, 14, 14, 31, 1, 1, 0, 1), "walk_wgrad"),     # 43 against 171
+    (0, (64, 96, 56, 56, 31, 1, 0, 1, 0), "walk_gather"),     # 127 against 312
+    (2, (8, 96, 224, 224, 31, 2, 0, 0, 0), "walk_wgrad"),     # 131 against 236
+    (3, (32, 80, 45, 37, 15, 1, 0, 0, 1), "walk_bwd"),        # 44 against 54
+    (0, (12, 247, 175, 15, 21, 1, 1, 0, 0), "gen_gather"),    # 117 against 96
+    (1, (12, 247, 175, 15, 21, 1, 1, 0, 0), "gen_gather"),
+    (0, (16, 64, 30, 30, 47, 1, 0, 1, 0), "gen_gather"),      # 35 against 32
+    (2, (49, 509, 10, 35, 9, 2, 1, 1, 0), "gen_wgrad"),       # 455 against 130
+    (1, (10, 499, 200, 9, 33, 1, 0, 1, 0), "gen_gather"),     # 566 against 175
+    (0, (48, 136, 58, 25, 27, 3, 1, 0, 0), "gen_gather"),     # 254 against 79
+    (1, (20, 262, 8, 60, 23, 1, 1, 0, 0), "gen_gather"),
+    (2, (20, 262, 8, 60, 23, 1, 1, 0, 0), "gen_wgrad"),       # 87 against 45
+    (0, (7, 68, 141, 141, 7, 1, 1, 0, 0), "gen_gather"),      # 126 against 67
+])
+def test_walks_where_they_are_faster(op, args, family):
+    assert _lib.kernel_name(op, *args).startswith(family + "/")
+
+
 def test_workspace_sizes_cover_every_route():
     # the workspace covers both the aligned and the unaligned route, and the _ex sizes the general kernels
     lib = _lib.lib()
