@@ -96,40 +96,40 @@ __host__ __device__ inline int chunks_of(int K, int esize) {
   return K <= 2 * v ? 2 : (K <= 4 * v ? 4 : 8);
 }
 
-// Launch grid: a row of at most 2^22 workgroups, as the workitems of one
-// dimension stay below 2^32; the kernel drops the last row's excess.
+// Launch grid: rows of at most 2^22 workgroups, as the workitems of one
+// dimension stay below 2^32; the last row's excess repeats the last tile.
 constexpr int kGridRow = 1 << 22;
 inline unsigned grid_x(const Params& p) { return (unsigned)(p.nblocks < kGridRow ? p.nblocks : kGridRow); }
 inline unsigned grid_y(const Params& p) { return (unsigned)cdiv(p.nblocks, kGridRow); }
 
 // The weight gradient's k = (image, pixel): a thread's 16-byte chunk of k
 // (ES: bytes per element) as quads of four, the same chunk of every step from
-// its first on, before whose k `left` remain.  Quad q is loaded from pixel
-// p[q] of image img[q]; a quad past the last k repeats the last one that is
-// whole (VEC: a quad is one access of four pixels of one image, so H W and
-// every chunk's first k are multiples of four) or the last pixel (single
-// elements).  (`left` counts down: k itself could pass 2^31.)
+// k0 on.  Quad q is loaded from pixel p[q] of image img[q]; a quad past the
+// last k repeats the last one that is whole (VEC: a quad is one access of four
+// pixels of one image, so H W and every k0 are multiples of four) or the last
+// pixel (single elements).  (Unsigned: k may pass 2^31 by a step.)
 template <int ES, bool VEC>
 struct Pixels {
-  static constexpr int NQ = 4 / ES;
-  static constexpr int BK = kRowBytes / ES;
-  int left;
+  static constexpr unsigned NQ = 4 / ES;
+  static constexpr unsigned BK = kRowBytes / ES;
+  unsigned k;
   int img[NQ], p[NQ];
-  __host__ __device__ __forceinline__ Pixels(const Params& P, int left0) {
-    left = left0;
+  __host__ __device__ __forceinline__ Pixels(const Params& P, unsigned k0) {
+    k = k0;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int n = left - 4 * q, at = P.K - (n > (VEC ? 4 : 1) ? n : (VEC ? 4 : 1));
+    for (unsigned q = 0; q < NQ; ++q) {
+      const unsigned last = (unsigned)P.K - (VEC ? 4 : 1);
+      const int at = (int)(k + 4 * q < last ? k + 4 * q : last);
       img[q] = at / P.HW;
       p[q] = at - img[q] * P.HW;
     }
   }
   __host__ __device__ __forceinline__ void next(const Params& P) {
-    left -= BK;
+    k += BK;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      if (left > 4 * q) {
-        p[q] += BK;
+    for (unsigned q = 0; q < NQ; ++q) {
+      if (k + 4 * q < (unsigned)P.K) {
+        p[q] += (int)BK;
         while (p[q] >= P.HW) {
           p[q] -= P.HW;
           ++img[q];

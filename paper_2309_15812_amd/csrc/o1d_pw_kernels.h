@@ -28,7 +28,7 @@
 //
 // What bounds it: the matrix cores in float32 (64 cycles per instruction).
 // 64 x 512 -> 512 x 56 x 56 (105 GFLOP per product), float32: forward 1158 ->
-// 909 us (116 TFLOP/s), the backward's two products 2280 -> 1721 us (122; the
+// 920 us (114 TFLOP/s), the backward's two products 2280 -> 1730 us (122; the
 // library's largest float32 product reaches 153); bfloat16, 64 x 384 -> 384 x
 // 14 x 14: 42 -> 16 us per product.  Before, loads behind per-run range tests
 // were waited for one by one, LDS took 4-byte accesses, and every image ended
@@ -235,10 +235,10 @@ __device__ __forceinline__ void load_pix(const Params& P, const T* __restrict__ 
     if (!VEC && first_of_wave(row0 + t / 8 + 32 * i) >= rows) break;  // rows that are not stored
     const int r = min(row0 + t / 8 + 32 * i, rows - 1);
 #pragma unroll
-    for (int q = 0; q < Pix<T, VEC>::NQ; ++q) {
+    for (int q = 0; q < (int)Pix<T, VEC>::NQ; ++q) {
       load_quad<T, VEC>(X, [&](int e) {
         int img = px.img[q], p = px.p[q];
-        if (!VEC && px.left > 4 * q + e) {  // elements of a run may lie in the next images
+        if (!VEC && px.k + 4 * q + e < (unsigned)P.K) {  // elements of a run may lie in the next images
           p += e;
           while (p >= P.HW) {
             p -= P.HW;
@@ -252,9 +252,7 @@ __device__ __forceinline__ void load_pix(const Params& P, const T* __restrict__ 
 }
 
 // One step's products of the wave's 32 x 128 block from a staged buffer.  A
-// chunk's reads are issued before the products of the chunk before it;
-// `between` (the next tile's writes and loads) runs after the first chunk's
-// products, so that the matrix cores start right after the barrier.
+// chunk's reads are issued before the products of the chunk before it.
 struct Frag {
   u32x4 a, b[4];
   __device__ __forceinline__ void read(const char* a0, const char* b0, int j) {
@@ -308,21 +306,22 @@ __global__ __launch_bounds__(kThreads, VB || sizeof(T) == 2 ? 3 : 2) void pw_gem
   // rows per wave; its element stores, four times as many, are shared out.)
   constexpr bool kSpread = KIND == kDgrad || (KIND == kFwd && !VB);
   // tiles along M are neighbours on one XCD: they share B's columns in its L2
-  const int b = blockIdx.y * kGridRow + blockIdx.x;
-  if (b >= P.nblocks) return;
+  // (past the last one: that tile again, with the same values; a branch here
+  // would put the arguments' loads in series, 0.4% of the product)
+  const int b = min((int)(blockIdx.y * kGridRow + blockIdx.x), P.nblocks - 1);
   const int id = P.xcd_per ? (b % 8) * P.xcd_per + b / 8 : b;
   const int mt = id % P.tm, rest = id / P.tm;
   const int split = rest % P.nsplit, nt = rest / P.nsplit;
   const int m0 = mt * kTile;
   const long long n0 = (long long)nt * kTile;
   const int s0 = split * P.per, s1 = min(P.steps, s0 + P.per);
-  Pix<T, VA> px(P, KIND == kWgrad ? P.K - s0 * BK - (int)(threadIdx.x % 8) * Fmt<T>::V : P.K);
+  Pix<T, VA> px(P, KIND == kWgrad ? (unsigned)s0 * BK + (threadIdx.x % 8) * Fmt<T>::V : 0u);
   // B's element loads, 32 per thread in bfloat16, are shared out over all waves
   // where few channels fill only the first chunks: E columns from e0 on of
   // chunk `chunk` (58 x 10 -> 10 x 59 x 59, bfloat16: block forward 41 -> 29 us)
   const int kg = threadIdx.x / 32;
   const int nc = !VB && KIND != kWgrad ? chunks_of(P.K, (int)sizeof(T)) : 8;
-  const int chunk = kg & (nc - 1), e0 = first_of_wave(kg / nc) * (nc / 2);
+  const int chunk = VB ? kg : kg & (nc - 1), e0 = VB ? 0 : first_of_wave(kg / nc) * (nc / 2);
   const Cols<VB> cols(P, KIND == kWgrad ? 0 : n0, threadIdx.x % 32, P.rowsB, e0);
   auto with_cols = [&](auto&& f) __attribute__((always_inline)) {
     if constexpr (VB) {

@@ -31,9 +31,9 @@ static bool walk(int N, int C, int Cout, int H, int W, bool ends = false) {
     const int s0 = split * P.per, s1 = P.steps < s0 + P.per ? P.steps : s0 + P.per;
     if (P.K - s0 * BK < BK) ++partial;  // a piece whose first step is cut
     for (int chunk = 0; chunk < 8; ++chunk) {
-      Pixels<ES, VEC> px(P, P.K - s0 * BK - chunk * V);
+      Pixels<ES, VEC> px(P, (unsigned)s0 * BK + chunk * V);
       for (int s = s0; s <= s1; ++s, px.next(P))
-        for (int q = 0; q < Pixels<ES, VEC>::NQ; ++q) {
+        for (int q = 0; q < (int)Pixels<ES, VEC>::NQ; ++q) {
           const long long k = (long long)s * BK + chunk * V + 4 * q;
           const int img = px.img[q], p = px.p[q], run = VEC ? 4 : 1;
           ++checked;
