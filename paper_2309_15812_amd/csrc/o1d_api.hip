@@ -13,8 +13,8 @@
 //    stride, both discretisations, the fused backward at stride 1 rounding
 //    down);
 //  * walk kernels (o1d_walk*.h): the strip kernels' walks for every layout,
-//    stride up to 3, either sampling and any plane (K <= 63): NHWC calls, and
-//    NCHW planes past the other two;
+//    stride up to 3, either sampling and any plane (K <= 63): calls past the
+//    other two that are estimated to be faster walked than with the tables;
 //  * general kernels (o1d_gen*.h): everything else the ABI accepts;
 //  * the depthwise separable block adds the pointwise convolution's matrix
 //    products on the matrix cores (o1d_pw*.h).
@@ -97,10 +97,10 @@ bool vec_aligned(const void* p, o1d_dtype_t dt) { return ((uintptr_t)p % (dt == 
 enum OpKind { kOpFwd = 0, kOpDgrad = 1, kOpWgrad = 2, kOpBwd = 3 };
 
 // The kernels one op runs: the strip kernels where they apply, else the
-// plane kernels, the walk kernels, the general kernels.  For the fused backward (kOpBwd)
-// the route is a one-pass kernel of the same order; where none applies (the
-// route is not ok) o1d_bwd runs the input gradient's route and then the
-// weight gradient's.
+// plane kernels, the walk kernels, the general kernels.  For the fused
+// backward (kOpBwd) the route is a one-pass kernel of the same order; where
+// none applies (the route is not ok) o1d_bwd runs the input gradient's route
+// and then the weight gradient's.
 enum class Family { None, Strip, Plane, Walk, Gen };
 
 struct Route {

@@ -1,7 +1,8 @@
 // Host-side plan of the walk kernels: forward pass, input gradient, weight
 // gradient and both gradients in one pass for either memory layout, stride
-// 1 .. 3, either sampling, any plane size and K <= 63 (NCHW planes that the
-// strip and plane kernels do not take, and every NHWC call).
+// 1 .. 3, either sampling, any plane size and K <= 63 (NHWC calls, and NCHW
+// planes that the strip and plane kernels do not take, where `applies` says
+// that they are faster than the table-driven general kernels).
 //
 // A team of 128 lanes (planes of at most 14 x 14: 64 lanes) works on one
 // channel, with the register-blocked walks of the strip kernels.  NCHW

@@ -1,4 +1,4 @@
-// Wave-level helpers shared by the general and plane kernels: compile-time
+// Wave-level helpers shared by the general, plane and walk kernels: compile-time
 // unrolled loops (per-cell sums must stay in registers, so their index must
 // be a constant) and the sum over a wave's 64 lanes of 32 values at once.
 #pragma once
