@@ -97,7 +97,7 @@ __host__ __device__ inline int chunks_of(int K, int esize) {
 }
 
 // Launch grid: rows of at most 2^22 workgroups, as the workitems of one
-// dimension stay below 2^32; the last row's excess repeats the last tile.
+// dimension stay below 2^32; the last row's excess stores nothing.
 constexpr int kGridRow = 1 << 22;
 inline unsigned grid_x(const Params& p) { return (unsigned)(p.nblocks < kGridRow ? p.nblocks : kGridRow); }
 inline unsigned grid_y(const Params& p) { return (unsigned)cdiv(p.nblocks, kGridRow); }

@@ -185,9 +185,9 @@ __device__ __forceinline__ void load_w_rc(const Params& P, const T* __restrict__
 // B of the forward and the input gradient, and their outputs: column (image,
 // pixel), rows HW apart.  Thread g's four columns of a tile (n0 on), which lie
 // at LDS rows g + 32 e: 4 g + e where they are one access (VEC), else g + 32 e
-// from e0 on, so that an element access covers consecutive pixels over the lanes.  off[e]:
-// element offset of column e (the last column's where there is none; off[0]
-// alone where VEC).
+// from e0 on, so that an element access covers consecutive pixels over the
+// lanes.  off[e]: element offset of column e (the last column's where there is
+// none; off[0] alone where VEC).
 template <bool VEC>
 struct Cols {
   long long off[4];
@@ -298,17 +298,18 @@ __device__ __forceinline__ void multiply(const char* buf, int chunks, f32x16 (&a
 
 // VA, VB: A's and B's (and the output's) runs of four elements are whole and aligned.
 template <typename T, int KIND, bool VA, bool VB>
-__global__ __launch_bounds__(kThreads, VB || sizeof(T) == 2 ? 3 : 2) void pw_gemm(Params P, const T* __restrict__ A, const T* __restrict__ B,
-                                                       void* __restrict__ out) {
+__global__ __launch_bounds__(kThreads, VB || sizeof(T) == 2 ? 3 : 2) void pw_gemm(Params P, const T* __restrict__ A,
+                                                                                  const T* __restrict__ B,
+                                                                                  void* __restrict__ out) {
   extern __shared__ __align__(16) char lds[];
   constexpr int BK = Fmt<T>::BK;
   // Rows of the output over the waves.  (The forward's vector stores keep 32
   // rows per wave; its element stores, four times as many, are shared out.)
   constexpr bool kSpread = KIND == kDgrad || (KIND == kFwd && !VB);
   // tiles along M are neighbours on one XCD: they share B's columns in its L2
-  // (past the last one: that tile again, with the same values; a branch here
-  // would put the arguments' loads in series, 0.4% of the product)
-  const int b = min((int)(blockIdx.y * kGridRow + blockIdx.x), P.nblocks - 1);
+  // (past the last one: that tile again, not stored; a branch here instead of
+  // at the end puts the arguments' loads in series, 0.4% of the product)
+  const int at = (int)(blockIdx.y * kGridRow + blockIdx.x), b = min(at, P.nblocks - 1);
   const int id = P.xcd_per ? (b % 8) * P.xcd_per + b / 8 : b;
   const int mt = id % P.tm, rest = id / P.tm;
   const int split = rest % P.nsplit, nt = rest / P.nsplit;
@@ -383,6 +384,7 @@ __global__ __launch_bounds__(kThreads, VB || sizeof(T) == 2 ? 3 : 2) void pw_gem
     __syncthreads();
     multiply<T, !VB && KIND != kWgrad>(lds, nc, acc);
   }
+  if (at >= P.nblocks) return;
   const int l = threadIdx.x & 63, r = l & 31, w = threadIdx.x >> 6;
   if constexpr (KIND == kWgrad) {
     float* o = static_cast<float*>(out) + (long long)split * P.M * P.N;

@@ -30,7 +30,7 @@
 // 56, K = 31, float32: forward 259 -> 128, weight gradient 277 -> 134; NHWC 64 x
 // 384 x 14 x 14, bfloat16: 86 -> 42, 171 -> 43; bilinear at the first shape: 312 ->
 // 136, 439 -> 154; stride 2 on 8 x 96 x 224 x 224: forward 218 -> 144, weight
-// gradient 236 -> 143; both gradients, 32 x 256 x 56 x 56, K = 63: 913 -> 278.
+// gradient 236 -> 143; both gradients, 32 x 256 x 56 x 56, K = 63: 913 -> 271.
 // What bounds them (stamped phases of NHWC 56 x 56, per plane and team): the
 // walk takes 6.6 us of 14.5, with two waves per SIMD too few to hide the
 // run starts' reloads; staging 4.2 and storing 2.7, where every lane of an
